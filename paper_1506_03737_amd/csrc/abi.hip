@@ -801,12 +801,12 @@ ForceProgram add_force(JobPack& jp, const std::vector<ForceBox>& boxes, const So
   return f;
 }
 
-// Tile sort of every box (counts cleared by a kernel, so the sequence may be recorded in a graph).
+// Tile sort of every box. The bucket counts are zero when it begins: clear_call zeroes them at the start of a call (before
+// the graph of a batched run), the scan leaves them zeroed for the next key pass.
 // keys_done: the key pass already ran (folded into the previous drift), so only the scan and the scatter remain
 void run_sort(const JobPack& jp, const SortSpace& ss, const Section& sec, int* flags, hipStream_t s,
               bool keys_done = false) {
   if (!keys_done) {
-    stage("sort keys", s, [&] { return kern::fill_i32(ss.cnt, static_cast<size_t>(ss.G), 0, s); });
     stage("sort keys", s, [&] {
       return kern::launch_tile_key(jp.jobs<kern::SortJob>(sec), jp.table(sec), ss.cnt, ss.key, ss.rank, flags, s);
     });
@@ -863,7 +863,6 @@ void run_cola(const JobPack& jp, const ForceProgram& f, const std::vector<double
     kd.cola = cola ? 1 : 0;
     // a drift is followed by a re-sort: its key pass runs inside this kernel, on zeroed bucket counts
     const bool keys = kd.do_drift != 0;
-    if (keys) stage("sort keys", s, [&] { return kern::fill_i32(f.ss.cnt, static_cast<size_t>(f.ss.G), 0, s); });
     if (lc && kd.do_drift && (*lc)[static_cast<size_t>(i)].tab) {
       stage("gather kick drift lightcone", s, [&] {
         return kern::launch_gather_kick_drift_lc(jp.jobs<kern::PartJob>(f.parts[c]), jp.table(f.parts[c]), kd,
@@ -947,13 +946,13 @@ lpc_status pm_force_impl(const lpc_geometry* geom, const lpc_stepping* step, con
   hipStream_t s = static_cast<hipStream_t>(stream);
   return guarded([&]() {
     int* flags = reinterpret_cast<int*>(ws);
-    stage("clear flags", s, [&] { return kern::fill_i32(flags, kern::kNumFlags, 0, s); });
     JobPack jp(at(ws, p.jobs));
     const ForceBox b = force_box(ws, p, geom->n_mesh, geom->box, n, const_cast<float*>(pos), nullptr, nullptr, nullptr,
                                  grad_out, reinterpret_cast<uint64_t*>(density_fixed_out));
     const ForceProgram f = add_force(jp, {b}, sort_space(ws, p, geom->n_mesh, LPC_OP_PM_FORCE, n), step->deconv_power,
                                      false);
     jp.upload(s);
+    stage("clear", s, [&] { return kern::clear_call(flags, f.ss.cnt, f.ss.G, s); });
     run_sort(jp, f.ss, f.sort_user, flags, s);
     run_force_mesh(jp, f, 0, flags, s);
     stage("gather", s, [&] { return kern::launch_gather(jp.jobs<kern::PartJob>(f.parts[0]), jp.table(f.parts[0]), flags, s); });
@@ -1157,13 +1156,13 @@ lpc_status lpc_cola_step(const lpc_geometry* geom, const lpc_cosmology* cosmo, c
   hipStream_t s = static_cast<hipStream_t>(stream);
   return guarded([&]() {
     int* flags = reinterpret_cast<int*>(ws);
-    stage("clear flags", s, [&] { return kern::fill_i32(flags, kern::kNumFlags, 0, s); });
     JobPack jp(at(ws, p.jobs));
     const ForceBox b = force_box(ws, p, geom->n_mesh, geom->box, inout->n, inout->pos, inout->vel, inout->psi1,
                                  inout->psi2, nullptr, nullptr);
     const ForceProgram f = add_force(jp, {b}, sort_space(ws, p, geom->n_mesh, LPC_OP_COLA_STEP, inout->n),
                                      step->deconv_power, true);
     jp.upload(s);
+    stage("clear", s, [&] { return kern::clear_call(flags, f.ss.cnt, f.ss.G, s); });
     run_cola(jp, f, tab, n_a, cosmo->omega_m, step->cola != 0, flags, s);
     return finish(flags, s);
   });
@@ -1215,7 +1214,6 @@ lpc_status lpc_cola_step_lightcone(const lpc_geometry* geom, const lpc_cosmology
     int* flags = reinterpret_cast<int*>(ws);
     // the record counter sits in the flag region (64 bytes in, 8 bytes)
     unsigned long long* counter = reinterpret_cast<unsigned long long*>(at(ws, 64));
-    stage("clear flags", s, [&] { return kern::fill_i32(flags, kern::kNumFlags, 0, s); });
     stage("clear flags", s, [&] { return kern::fill_i32(reinterpret_cast<int*>(counter), 2, 0, s); });
     JobPack jp(at(ws, p.jobs));
     const ForceBox b = force_box(ws, p, geom->n_mesh, geom->box, inout->n, inout->pos, inout->vel, inout->psi1,
@@ -1285,6 +1283,7 @@ lpc_status lpc_cola_step_lightcone(const lpc_geometry* geom, const lpc_cosmology
       L.capacity = lc->capacity;
     }
     jp.upload(s);
+    stage("clear", s, [&] { return kern::clear_call(flags, f.ss.cnt, f.ss.G, s); });
     run_cola(jp, f, tab, n_a, cosmo->omega_m, cola, flags, s, &lcs);
     unsigned long long cnt = 0;
     check(hipMemcpyAsync(&cnt, counter, sizeof(cnt), hipMemcpyDeviceToHost, s), "hipMemcpyAsync(count)");
@@ -1361,7 +1360,6 @@ lpc_status lpc_cola_step_batched(const lpc_batch_entry* entries, int32_t n_real,
   hipStream_t s = static_cast<hipStream_t>(stream);
   return guarded([&]() {
     int* flags = reinterpret_cast<int*>(ws);
-    stage("clear flags", s, [&] { return kern::fill_i32(flags, kern::kNumFlags, 0, s); });
     JobPack jp(at(ws, round_up(sizeof(int) * kern::kNumFlags)));  // the job region follows the flags
     std::vector<ForceBox> boxes;
     for (int i = 0; i < n_real; ++i) {
@@ -1387,6 +1385,7 @@ lpc_status lpc_cola_step_batched(const lpc_batch_entry* entries, int32_t n_real,
     }
     const ForceProgram f = add_force(jp, boxes, ss, step->deconv_power, true);
     jp.upload(s);
+    stage("clear", s, [&] { return kern::clear_call(flags, f.ss.cnt, f.ss.G, s); });
     const bool cola = step->cola != 0;
     if (!g_graph_on || g_prof.on) {
       run_cola(jp, f, tab, n_a, cosmo->omega_m, cola, flags, s);
@@ -1696,7 +1695,7 @@ lpc_status lpc_power_spectrum(const lpc_geometry* geom, const float* pos, int64_
     JobPack jp(at(ws, p.jobs));
     const DensitySpectrum ds = add_density_spectrum(jp, ws, p, geom, pos, n, LPC_OP_POWER_SPECTRUM, A);
     jp.upload(s);
-    stage("clear flags", s, [&] { return kern::fill_i32(flags, kern::kNumFlags, 0, s); });
+    stage("clear", s, [&] { return kern::clear_call(flags, ds.ss.cnt, ds.ss.G, s); });
     stage("clear bins", s, [&] {
       return kern::fill_i32(reinterpret_cast<int*>(sums), static_cast<size_t>(6) * n_bins, 0, s);
     });
@@ -1751,7 +1750,7 @@ lpc_status lpc_bispectrum(const lpc_geometry* geom, const float* pos, int64_t n,
     const C2RSections inv[3] = {add_c2r(jp, H, nm, F[0], 1.f), add_c2r(jp, H, nm, F[1], 1.f),
                                 add_c2r(jp, H, nm, F[2], 1.f)};
     jp.upload(s);
-    stage("clear flags", s, [&] { return kern::fill_i32(flags, kern::kNumFlags, 0, s); });
+    stage("clear", s, [&] { return kern::clear_call(flags, ds.ss.cnt, ds.ss.G, s); });
     run_density_spectrum(jp, ds, flags, s);
     for (int t = 0; t < m; ++t) {
       double* pt = parts + static_cast<size_t>(t) * kPartsPerTriangle * nb;

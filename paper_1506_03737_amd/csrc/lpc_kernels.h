@@ -76,6 +76,8 @@ struct LightconeStep {
 };
 
 hipError_t fill_i32(int* p, size_t count, int value, hipStream_t s);
+// Zeroes the error flags and `count` bucket counts: the first launch of a call that sorts particles.
+hipError_t clear_call(int* flags, int* cnt, int count, hipStream_t s);
 
 // ---------------------------------------------------------------------------------------------------------------
 // Batched stage launches. Every stage kernel runs over the items of a work table: FFT kernels take one item per
@@ -277,7 +279,8 @@ size_t lds_z_c2r(int n, int B);
 hipError_t launch_tile_key(const SortJob* jobs, WorkTable wt, int* cnt, int* key, int* rank, int* flags,
                            hipStream_t s);
 int scan_blocks(int count);  // entries of the block-sum scratch of launch_scan
-hipError_t launch_scan(const int* cnt, int* start, int count, int* block_sums, hipStream_t s);  // start: count + 1
+// start: count + 1 entries; cnt is left zeroed
+hipError_t launch_scan(int* cnt, int* start, int count, int* block_sums, hipStream_t s);
 hipError_t launch_scatter(const SortJob* jobs, WorkTable wt, const int* key, const int* rank, const int* start,
                           hipStream_t s);
 hipError_t launch_deposit_tiles(const DepJob* jobs, WorkTable wt, const int* start, int* flags, hipStream_t s);

@@ -97,6 +97,13 @@ __global__ __launch_bounds__(kNT) void k_fill_i32(int* __restrict__ p, size_t co
   for (size_t i = static_cast<size_t>(blockIdx.x) * kNT + threadIdx.x; i < count; i += stride) p[i] = value;
 }
 
+// Zeroes the error flags and the sort's bucket counts at the start of a call.
+__global__ __launch_bounds__(kNT) void k_clear(int* __restrict__ flags, int* __restrict__ cnt, int count) {
+  const int i = blockIdx.x * kNT + threadIdx.x;
+  if (i < kNumFlags) flags[i] = 0;
+  if (i < count) cnt[i] = 0;
+}
+
 // ---------------------------------------------------------------------------------------------------------------
 // Tile sort. A box's mesh is cut into tiles of kTX x kTY x kTZ cells (the last tile of an axis may be narrower); a
 // particle belongs to the tile of its floor cell, and within it to one of two buckets: interior, or boundary when its
@@ -118,95 +125,163 @@ __device__ __forceinline__ int bucket_of(uint32_t cx, uint32_t cy, uint32_t cz, 
 
 // Rank of each active thread among the threads of its workgroup with the same bucket g, with one counter atomic per
 // distinct bucket in the workgroup: longer runs of one bucket in the sorted copy than a wave's (fewer partial cache
-// lines written by the scatter). Wave runs of one bucket are merged through an LDS hash of the block's buckets
-// (kRankSlots >= 2 kNT slots, linear probing, so an insert always finds a slot); LDS atomics give each run its offset
-// in the block, and the leader thread of each slot takes the block's range from cnt. Called by all threads of the
-// workgroup (it has barriers); sh holds 3 kRankSlots ints.
-constexpr int kRankSlots = 2 * kNT;
-__device__ int block_rank(int* __restrict__ cnt, int g, bool active, int* sh) {
+// lines written by the scatter). The block's buckets go into an LDS hash (two slots a key, linear probing, so an insert
+// always finds a slot); LDS atomics give each thread its offset in the block, and the leader thread of each
+// slot takes the block's range from cnt. The threads of a wave that share the bucket of its first thread enter as one
+// group (a sorted set's waves mostly hold one bucket, and 64 atomics on one address would run one by one); all others
+// probe at once. One bucket after another (a ballot, two LDS atomics and four shuffles in a chain each) bound the key
+// pass of unsorted particles: 16.7 M of a 256^3 lattice at a = 1 on 512^3 took 335 us that way. Called by all threads of
+// the workgroup (it has barriers); sh holds BlockRank<U>::kInts ints.
+// U keys per thread: a pass that ranks U kNT particles per workgroup merges more of them into one counter atomic.
+template <int U>
+struct BlockRank {
+  static constexpr int kSlots = 2 * kNT * U, kInts = 3 * kSlots;
+};
+template <int U>
+__device__ __forceinline__ void block_rank(int* __restrict__ cnt, const int (&g)[U], const bool (&active)[U], int* sh,
+                                           int (&rank)[U]) {
+  constexpr int kSlots = BlockRank<U>::kSlots;
   int* s_key = sh;
-  int* s_cnt = sh + kRankSlots;
-  int* s_base = sh + 2 * kRankSlots;
-  for (int t = threadIdx.x; t < kRankSlots; t += kNT) {
+  int* s_cnt = sh + kSlots;
+  int* s_base = sh + 2 * kSlots;
+  for (int t = threadIdx.x; t < kSlots; t += kNT) {
     s_key[t] = -1;
     s_cnt[t] = 0;
   }
   __syncthreads();
   const int lane = __lane_id();
   const unsigned long long below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  unsigned long long pending = __ballot(active);
-  int slot = 0, local = 0;
-  while (pending) {
-    const int leader = __ffsll(static_cast<long long>(pending)) - 1;
-    const int lg = __shfl(g, leader);
-    const unsigned long long same = __ballot(active && g == lg);
-    int sl = 0, off = 0;
-    if (lane == leader) {
-      sl = static_cast<int>((static_cast<unsigned>(lg) * 2654435761u) % kRankSlots);
-      while (true) {
-        const int prev = atomicCAS(s_key + sl, -1, lg);
-        if (prev == -1 || prev == lg) break;
-        sl = (sl + 1) % kRankSlots;
+  int slot[U], local[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    slot[u] = local[u] = 0;
+    const unsigned long long mask = __ballot(active[u]);
+    if (mask) {  // uniform over the wave
+      const int leader = __ffsll(static_cast<long long>(mask)) - 1;
+      const int lg = __shfl(g[u], leader);
+      const bool in_group = active[u] && g[u] == lg;
+      const unsigned long long same = __ballot(in_group);
+      if (active[u] && (lane == leader || !in_group)) {
+        int sl = static_cast<int>((static_cast<unsigned>(g[u]) * 2654435761u) % kSlots);
+        while (true) {
+          const int prev = atomicCAS(s_key + sl, -1, g[u]);
+          if (prev == -1 || prev == g[u]) break;
+          sl = (sl + 1) % kSlots;
+        }
+        slot[u] = sl;
+        local[u] = atomicAdd(s_cnt + sl, lane == leader ? __popcll(same) : 1);
       }
-      off = atomicAdd(s_cnt + sl, __popcll(same));
+      const int gslot = __shfl(slot[u], leader), glocal = __shfl(local[u], leader);
+      if (in_group) {
+        slot[u] = gslot;
+        local[u] = glocal + __popcll(same & below);
+      }
     }
-    sl = __shfl(sl, leader);
-    off = __shfl(off, leader);
-    if (active && g == lg) {
-      slot = sl;
-      local = off + __popcll(same & below);
-    }
-    pending &= ~same;
   }
   __syncthreads();
-  for (int t = threadIdx.x; t < kRankSlots; t += kNT)
+  for (int t = threadIdx.x; t < kSlots; t += kNT)
     if (s_key[t] >= 0) s_base[t] = atomicAdd(cnt + s_key[t], s_cnt[t]);
   __syncthreads();
-  const int rank = active ? s_base[slot] + local : 0;
+#pragma unroll
+  for (int u = 0; u < U; ++u) rank[u] = active[u] ? s_base[slot[u]] + local[u] : 0;
   __syncthreads();  // sh is reused by the next call
-  return rank;
 }
 
+// A workgroup keys kKeyItems consecutive items of one box (a box's items are a multiple of 8): with one item each, the
+// chain of position load, rank atomic (a round trip to memory) and store, at 2048 workgroups in flight, bound the pass.
+constexpr int kKeyItems = 4;
 __global__ __launch_bounds__(kNT) void k_tile_key(const SortJob* __restrict__ jobs, const int* __restrict__ offs,
                                                   int njob, int total, int* __restrict__ cnt, int* __restrict__ key,
                                                   int* __restrict__ rank, int* __restrict__ flags) {
-  __shared__ int sh[3 * kRankSlots];
-  for (int w = blockIdx.x; w < total; w += gridDim.x) {
-    const int jb = __builtin_amdgcn_readfirstlane(find_job(to_const(offs), njob, w));
-    const LPC_CONST SortJob& J = to_const(jobs)[jb];
-    const int64_t n = J.n;
-    const int64_t i = static_cast<int64_t>(xcd_remap(w - offs[jb], offs[jb + 1] - offs[jb])) * kNT + threadIdx.x;
-    const bool active = i < n;
-    int g = 0;
-    if (active) {
-      LPC_GLOBAL const float* pos = to_global(J.pos);
-      const int64_t period = static_cast<int64_t>(J.nm) << kFracBits;
-      float x[3];  // the three loads go out together
+  __shared__ int sh[BlockRank<kKeyItems>::kInts];
+  const int w = blockIdx.x * kKeyItems;
+  if (w >= total) return;
+  const int jb = __builtin_amdgcn_readfirstlane(find_job(to_const(offs), njob, w));
+  const LPC_CONST SortJob& J = to_const(jobs)[jb];
+  const int64_t n = J.n;
+  const int group = xcd_remap((w - offs[jb]) / kKeyItems, (offs[jb + 1] - offs[jb]) / kKeyItems);
+  const int64_t i0 = static_cast<int64_t>(group) * (kKeyItems * kNT) + threadIdx.x;
+  if (i0 - threadIdx.x >= n) return;  // padding items (uniform)
+  LPC_GLOBAL const float* pos = to_global(J.pos);
+  const int64_t period = static_cast<int64_t>(J.nm) << kFracBits;
+  float x[kKeyItems][3];  // every load goes out before the first is used (past the end: the last particle's)
 #pragma unroll
-      for (int d = 0; d < 3; ++d) x[d] = pos[d * n + i];
+  for (int u = 0; u < kKeyItems; ++u) {
+    const int64_t i = min(i0 + u * kNT, n - 1);
+#pragma unroll
+    for (int d = 0; d < 3; ++d) x[u][d] = pos[d * n + i];
+  }
+  int g[kKeyItems], r[kKeyItems];
+  bool active[kKeyItems];
+#pragma unroll
+  for (int u = 0; u < kKeyItems; ++u) {
+    active[u] = i0 + u * kNT < n;
+    g[u] = 0;
+    if (active[u]) {
       uint32_t c[3], f[3];
-      bool ok = true;
-#pragma unroll
-      for (int d = 0; d < 3; ++d) ok &= fixed_coord(x[d], J.scale, period, &c[d], &f[d]);
       int b = 2 * J.ntx * J.nty * J.ntz;
-      if (ok)
+      if (fixed_coord3(x[u], J.scale, period, c, f))
         b = bucket_of(c[0], c[1], c[2], J);
       else
         atomicOr(flags + kFlagNonfinite, 1);
-      g = J.tbase + b;
+      g[u] = J.tbase + b;
     }
-    const int r = block_rank(cnt, g, active, sh);
-    if (active) {
-      key[J.pbase + i] = g;
-      rank[J.pbase + i] = r;
+  }
+  block_rank<kKeyItems>(cnt, g, active, sh, r);
+#pragma unroll
+  for (int u = 0; u < kKeyItems; ++u) {
+    if (active[u]) {
+      key[J.pbase + i0 + u * kNT] = g[u];
+      rank[J.pbase + i0 + u * kNT] = r[u];
     }
   }
 }
 
-// Exclusive scan of cnt[0..count) into start[0..count] in three launches: block-local scans of kScanBlock elements
-// (writing block totals), a scan of the block totals, and the add of each block's offset.
+// Exclusive scan of cnt[0..count) into start[0..count], which also zeroes cnt for the next key pass (one launch fewer per
+// sort). Up to kScanOne buckets (meshes up to 320^3) one workgroup does it in one launch; more take three: block-local
+// scans of kScanBlock elements (writing block totals), a scan of the block totals, and the add of each block's offset.
 constexpr int kScanPer = 8;
 constexpr int kScanBlock = kNT * kScanPer;
+constexpr int kScanNT = 1024, kScanOnePer = 16;
+constexpr int kScanOne = kScanNT * kScanOnePer;
+
+__global__ __launch_bounds__(kScanNT) void k_scan_one(int* __restrict__ cnt, int* __restrict__ start, int count) {
+  __shared__ int waves[kScanNT / 64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int per = (count + kScanNT - 1) / kScanNT, base = tid * per;  // per <= kScanOnePer (uniform)
+  int v[kScanOnePer];
+  int sum = 0;
+#pragma unroll
+  for (int k = 0; k < kScanOnePer; ++k) {
+    v[k] = 0;
+    if (k < per && base + k < count) {
+      v[k] = cnt[base + k];
+      cnt[base + k] = 0;
+    }
+    sum += v[k];
+  }
+  int incl = sum;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int u = __shfl_up(incl, off);
+    if (lane >= off) incl += u;
+  }
+  if (lane == 63) waves[wave] = incl;
+  __syncthreads();
+  int before = 0, total = 0;
+#pragma unroll
+  for (int w = 0; w < kScanNT / 64; ++w) {
+    if (w < wave) before += waves[w];
+    total += waves[w];
+  }
+  int run = before + incl - sum;
+#pragma unroll
+  for (int k = 0; k < kScanOnePer; ++k) {
+    if (k < per && base + k < count) start[base + k] = run;
+    run += v[k];
+  }
+  if (tid == 0) start[count] = total;
+}
 
 __device__ __forceinline__ int block_exclusive_scan(int v, int* sh, int* total) {
   // sh: kNT ints of LDS; Hillis-Steele over the workgroup
@@ -225,7 +300,7 @@ __device__ __forceinline__ int block_exclusive_scan(int v, int* sh, int* total) 
   return incl - v;
 }
 
-__global__ __launch_bounds__(kNT) void k_scan_local(const int* __restrict__ cnt, int* __restrict__ start, int count,
+__global__ __launch_bounds__(kNT) void k_scan_local(int* __restrict__ cnt, int* __restrict__ start, int count,
                                                     int* __restrict__ block_sums) {
   __shared__ int sh[kNT];
   const int base = blockIdx.x * kScanBlock + threadIdx.x * kScanPer;
@@ -233,7 +308,11 @@ __global__ __launch_bounds__(kNT) void k_scan_local(const int* __restrict__ cnt,
   int sum = 0;
 #pragma unroll
   for (int k = 0; k < kScanPer; ++k) {
-    v[k] = (base + k < count) ? cnt[base + k] : 0;
+    v[k] = 0;
+    if (base + k < count) {
+      v[k] = cnt[base + k];
+      cnt[base + k] = 0;
+    }
     sum += v[k];
   }
   int total;
@@ -735,7 +814,7 @@ __global__ __launch_bounds__(kNT) void k_gather_kick_drift(const PartJob* __rest
                                                            KickDrift kd, LightconeStep lc, int* __restrict__ flags,
                                                            int* __restrict__ cnt, int* __restrict__ key,
                                                            int* __restrict__ rank) {
-  __shared__ int sh[3 * kRankSlots];  // block_rank, when key != NULL
+  __shared__ int sh[BlockRank<1>::kInts];  // block_rank, when key != NULL
   for (int w = blockIdx.x; w < total; w += gridDim.x) {
     const int jb = __builtin_amdgcn_readfirstlane(find_job(to_const(offs), njob, w));
     const LPC_CONST PartJob& J = to_const(jobs)[jb];
@@ -801,7 +880,8 @@ __global__ __launch_bounds__(kNT) void k_gather_kick_drift(const PartJob* __rest
       lightcone_test(lc, kd, J.box, lc_ok, xs, xe, vv, q1, q2, index, lsm);
     }
     if (key) {  // uniform: the next sort's key pass on the positions as stored (k_tile_key's arithmetic)
-      int g = 0;
+      int g[1] = {0}, r[1];
+      const bool act[1] = {active};
       if (active) {
         const int64_t period = static_cast<int64_t>(J.nm) << kFracBits;
         uint32_t c[3], f[3];
@@ -813,12 +893,12 @@ __global__ __launch_bounds__(kNT) void k_gather_kick_drift(const PartJob* __rest
           b = bucket_of(c[0], c[1], c[2], J);
         else
           atomicOr(flags + kFlagNonfinite, 1);
-        g = J.tbase + b;
+        g[0] = J.tbase + b;
       }
-      const int r = block_rank(cnt, g, active, sh);
+      block_rank<1>(cnt, g, act, sh, r);
       if (active) {
-        key[J.pbase + i] = g;
-        rank[J.pbase + i] = r;
+        key[J.pbase + i] = g[0];
+        rank[J.pbase + i] = r[0];
       }
     }
   }
@@ -872,18 +952,29 @@ hipError_t fill_i32(int* p, size_t count, int value, hipStream_t s) {
   return hipGetLastError();
 }
 
+hipError_t clear_call(int* flags, int* cnt, int count, hipStream_t s) {
+  const int m = count > kNumFlags ? count : static_cast<int>(kNumFlags);
+  k_clear<<<static_cast<unsigned>((m + kNT - 1) / kNT), kNT, 0, s>>>(flags, cnt, count);
+  return hipGetLastError();
+}
+
 hipError_t launch_tile_key(const SortJob* jobs, WorkTable wt, int* cnt, int* key, int* rank, int* flags,
                            hipStream_t s) {
   if (wt.total <= 0) return hipSuccess;
-  k_tile_key<<<grid_of(wt), kNT, 0, s>>>(jobs, wt.offs, wt.njob, wt.total, cnt, key, rank, flags);
+  static_assert(8 % kKeyItems == 0, "a box's items are a multiple of 8");
+  k_tile_key<<<grid_of(wt) / kKeyItems, kNT, 0, s>>>(jobs, wt.offs, wt.njob, wt.total, cnt, key, rank, flags);
   return hipGetLastError();
 }
 
 int scan_blocks(int count) { return (count + kScanBlock - 1) / kScanBlock; }
 
-hipError_t launch_scan(const int* cnt, int* start, int count, int* block_sums, hipStream_t s) {
+hipError_t launch_scan(int* cnt, int* start, int count, int* block_sums, hipStream_t s) {
   const int nb = scan_blocks(count);
   if (nb == 0) return hipErrorInvalidValue;
+  if (count <= kScanOne) {
+    k_scan_one<<<1, kScanNT, 0, s>>>(cnt, start, count);
+    return hipGetLastError();
+  }
   k_scan_local<<<nb, kNT, 0, s>>>(cnt, start, count, block_sums);
   k_scan_sums<<<1, kNT, 0, s>>>(block_sums, nb, start, count);
   k_scan_add<<<nb, kNT, 0, s>>>(start, count, block_sums);
