@@ -1511,59 +1511,164 @@ lpc_status init_ic_impl(const lpc_geometry* geom, const lpc_cosmology* cosmo, ui
   hipStream_t s = static_cast<hipStream_t>(stream);
   return guarded([&]() {
     const host::Cosmo c = to_host(cosmo);
-    const double A = host::pk_amplitude(c);
     int* flags = reinterpret_cast<int*>(ws);
     stage("clear flags", s, [&] { return kern::fill_i32(flags, kern::kNumFlags, 0, s); });
-    const int pitch = kern::mesh_pitch(N);
-    float2* dhat = reinterpret_cast<float2*>(at(ws, p.A));
-    float2* spec = reinterpret_cast<float2*>(at(ws, p.B));
-    float2* nlhat = reinterpret_cast<float2*>(at(ws, p.C));
-    float* r0 = out->psi2;
-    float* r1 = out->psi2 + n;
-    float* r2 = out->psi2 + 2 * n;
+    const int pitch = kern::mesh_pitch(N), h = N / 2;
+    const double box = geom->box, kf = 2.0 * M_PI / box;
+    const double norm = static_cast<double>(N) * N * N / (box * box * box);
     const float inv_n3 = static_cast<float>(1.0 / static_cast<double>(n));
-    // the transforms of the whole construction, in order: r2c(noise), 12 derived fields, r2c(source), and the 2LPT
-    // displacement fields; kinds 0..2 Psi1, 3..8 phi1_ij, 9..11 Psi2
-    float* dst[12] = {out->psi1, out->psi1 + n, out->psi1 + 2 * n, r0, r1, r2, r1, r1, r1, r0, r1, r2};
+    // Spectra: three in the workspace, three in output arrays that are written last (12 n bytes each hold a spectrum and
+    // its alignment at every N >= 8); the weight tables (48 N^2 bytes at most) take such an array too.
+    auto in_array = [](float* p) { return reinterpret_cast<char*>((reinterpret_cast<uintptr_t>(p) + 63) & ~uintptr_t(63)); };
+    float2* A = reinterpret_cast<float2*>(at(ws, p.A));
+    float2* B = reinterpret_cast<float2*>(at(ws, p.B));
+    float2* C = reinterpret_cast<float2*>(at(ws, p.C));
+    float2* P = reinterpret_cast<float2*>(in_array(out->pos));
+    float2* V = reinterpret_cast<float2*>(in_array(out->vel));
+    float2* D = reinterpret_cast<float2*>(in_array(out->psi2));
+    const int n2_count = 3 * h * h + 1;
     JobPack jp(at(ws, p.jobs));
-    const R2CSections noise = add_r2c(jp, r0, false, 0.0, N, dhat);
-    C2RSections der[12];
-    for (int k = 0; k < 12; ++k) der[k] = add_c2r(jp, spec, N, dst[k], inv_n3);
-    const R2CSections source = add_r2c(jp, r0, false, 0.0, N, dhat);
-    // non-Gaussian stage: real fields D^a phi in the five slots psi1[0..2], psi2[1..2]; products in psi2[0]
-    float* slot[5] = {out->psi1, out->psi1 + n, out->psi1 + 2 * n, r1, r2};
-    std::vector<C2RSections> to_real;
-    std::vector<R2CSections> prod_r2c;
-    for (size_t v = 0; v < alphas.size(); ++v) to_real.push_back(add_c2r(jp, spec, N, slot[v], inv_n3));
-    for (size_t v = 0; v < gammas.size(); ++v) prod_r2c.push_back(add_r2c(jp, r0, false, 0.0, N, spec));
-    jp.upload(s);
-    auto derived = [&](int kind) {
-      stage("spectral factor", s, [&] { return kern::ic_spectral_factor(dhat, spec, N, pitch, geom->box, kind, s); });
-      run_c2r(jp, der[kind], s);
+    const Plan1D full = plan_of(N), hplan = plan_of(h);
+    const float2 *tw = jp.twiddles(full), *twh = jp.twiddles(hplan), *roots = jp.half_roots(N);
+    const int Bax = tiling_of(N).axis_cols, Pax = kern::axis_points(N, Bax);
+    const size_t lds_ax = kern::lds_axis(N, Bax);
+    // forward y pass of meshes m[0..count), without the kz = N / 2 column
+    auto y_forward = [&](float2* const* m, int count) {
+      std::vector<kern::AxisJob> jobs;
+      std::vector<int> items;
+      for (int i = 0; i < count; ++i) {
+        kern::AxisJob y = axis_job(jp, m[i], N, pitch, static_cast<int64_t>(N) * pitch, 0, Bax);
+        y.ncols = h;
+        y.ntc = (h + Bax - 1) / Bax;
+        y.per_comp = round8(N * y.ntc);
+        jobs.push_back(y);
+        items.push_back(y.per_comp);
+      }
+      return jp.add(jobs, items);
     };
-    stage("noise", s, [&] { return kern::ic_noise(seed, N, r0, s); });
-    run_r2c(jp, noise, false, flags, s);
+    auto run_y = [&](const Section& sec, bool inverse) {
+      stage(inverse ? "ic y inv" : "ic y", s, [&] {
+        return kern::launch_axis(jp.jobs<kern::AxisJob>(sec), jp.table(sec), inverse, Bax, Pax, lds_ax, s);
+      });
+    };
+    const Section y_noise = y_forward(&A, 1);
+    float2* png_mesh[4] = {B, C, P, V};
+    const Section y_fields[3] = {y_forward(png_mesh, 1), y_forward(png_mesh, 2), y_forward(png_mesh, 3)};
+    const Section y_groups = y_forward(png_mesh, std::max<int>(1, static_cast<int>(gammas.size())));
+    kern::YGradJob yg{};
+    yg.A = A;
+    yg.B = B;
+    yg.C = C;
+    yg.astr = pitch;
+    yg.ostr = static_cast<int64_t>(N) * pitch;
+    yg.n = N;
+    yg.ncols = h;
+    yg.ntc = (h + Bax - 1) / Bax;
+    yg.per_comp = round8(N * yg.ntc);
+    yg.ntc1 = (h + Bax / 2 - 1) / (Bax / 2);
+    yg.per_comp1 = round8(N * yg.ntc1);
+    yg.kf = static_cast<float>(kf);
+    yg.pl = full;
+    yg.tw = tw;
+    const Section y_psi2 = jp.add1(yg, yg.per_comp + yg.per_comp1);
+    double gl[128];
+    host::gauss_legendre64(gl, gl + 64);
+    const double* gl_dev = static_cast<const double*>(jp.data(gl, sizeof(gl)));
+    const std::vector<double> none(kern::kIcPieces, 0.0);
+    double* sigma8_parts = static_cast<double*>(const_cast<void*>(jp.data(none.data(), none.size() * sizeof(double))));
+    jp.upload(s);
+    stage("ic sigma8", s, [&] { return kern::ic_sigma8(gl_dev, c.n_s, c.omega_m * c.h, sigma8_parts, s); });
+
+    kern::IcR2C zf{};
+    zf.tw = twh;
+    zf.roots = roots;
+    zf.pl = hplan;
+    zf.N = N;
+    zf.pitch = pitch;
+    zf.seed = seed;
+    zf.out[0] = A;
+    stage("ic noise", s, [&] { return kern::ic_r2c(zf, true, 1, s); });
+    run_y(y_noise, false);
+    auto weights = [&](void* table, const std::vector<kern::IcWeight>& spec) {
+      kern::IcWeights w{};
+      w.table = static_cast<double*>(table);
+      w.count = n2_count;
+      w.kf = kf;
+      w.om_h = c.omega_m * c.h;
+      w.sigma8 = c.sigma8;
+      w.sigma8_parts = sigma8_parts;
+      std::copy(spec.begin(), spec.end(), w.spec);
+      stage("ic weights", s, [&] { return kern::ic_weights(w, static_cast<int>(spec.size()), s); });
+      return static_cast<const double*>(w.table);
+    };
+    kern::IcX x0{};
+    x0.N = N;
+    x0.pitch = pitch;
+    x0.kf = static_cast<float>(kf);
+    x0.sign = 1.f;
+    x0.tw = tw;
+    x0.pl = full;
+    kern::IcZ zi{};
+    zi.tw = twh;
+    zi.roots = roots;
+    zi.pl = hplan;
+    zi.N = N;
+    zi.pitch = pitch;
+    zi.kf = static_cast<float>(kf);
+    zi.scale = inv_n3;
+    zi.box = box;
+    zi.psi1 = out->psi1;
+    zi.psi2 = out->psi2;
+    zi.pos = out->pos;
+    zi.vel = out->vel;
+    zi.id = out->id;
+    zi.aligned = ((reinterpret_cast<uintptr_t>(out->psi1) | reinterpret_cast<uintptr_t>(out->psi2) |
+                   reinterpret_cast<uintptr_t>(out->pos) | reinterpret_cast<uintptr_t>(out->vel)) & 7) == 0;
+
+    kern::IcX xd = x0;  // delta_L / k^2 and its x derivatives
     if (!png) {
-      stage("scale spectrum", s, [&] { return kern::ic_scale_spectrum(dhat, N, pitch, geom->box, A, c.omega_m, c.h, c.n_s, s); });
+      const double* w = weights(D, {{norm, c.n_s, 2, 1, 1}});
+      xd.nin = 1;
+      xd.in[0] = A;
+      xd.w[0] = w;
     } else {
       // Phi = phi + fNL sum_j c_j D^g[(D^a phi)(D^b phi)], D^s = k^(s (4 - ns) / 3); delta_L = alpha0 k^2 T Phi
       const double g0 = host::growth_suppression(c);
       const double alpha0 = (2.0 / 3.0) * host::kCOverH0 * host::kCOverH0 * g0 / c.omega_m;
-      const double a_phi = A / (alpha0 * alpha0);
       const double tilt = (4.0 - c.n_s) / 3.0;
-      stage("png potential", s, [&] { return kern::png_potential(dhat, N, pitch, geom->box, a_phi, c.n_s, s); });
-      for (size_t v = 0; v < alphas.size(); ++v) {
-        stage("png power", s, [&] {
-          return kern::png_power(dhat, spec, N, pitch, geom->box, alphas[v] * tilt, 1.0, false, s);
-        });
-        run_c2r(jp, to_real[v], s);
+      std::vector<kern::IcWeight> spec{{norm / (alpha0 * alpha0), c.n_s - 4.0, 0, 1, 1}};
+      for (double e : alphas) spec.push_back({1.0, e * tilt, 0, 0, 0});
+      const double* w = weights(V, spec);
+      // real fields D^a phi in psi1 and psi2, three at a time (phi stays in A)
+      float* slot[6] = {out->psi1, out->psi1 + n, out->psi1 + 2 * n, out->psi2, out->psi2 + n, out->psi2 + 2 * n};
+      for (size_t first = 0; first < alphas.size(); first += 3) {
+        const int count = static_cast<int>(std::min<size_t>(3, alphas.size() - first));
+        kern::IcX xa = x0;
+        if (first == 0) {
+          xa.nin = 1;
+          xa.in[0] = A;
+          xa.w[0] = w;
+          xa.keep = A;
+        } else {
+          xa.base = A;  // weight 1
+        }
+        xa.nout = count;
+        kern::IcZ za = zi;
+        for (int o = 0; o < count; ++o) {
+          xa.out[o] = png_mesh[o];
+          xa.wout[o] = w + (first + o + 1) * static_cast<size_t>(n2_count);
+          za.in[o] = png_mesh[o];
+          za.real[o] = slot[first + o];
+        }
+        stage("ic x", s, [&] { return kern::ic_x(xa, s); });
+        run_y(y_fields[count - 1], true);
+        stage("ic z inv", s, [&] { return kern::ic_z(za, kern::kIcPlain, count, s); });
       }
-      auto field = [&](double e) {
-        return slot[std::find(alphas.begin(), alphas.end(), e) - alphas.begin()];
-      };
+      auto field = [&](double e) { return slot[std::find(alphas.begin(), alphas.end(), e) - alphas.begin()]; };
+      kern::IcR2C zp = zf;
+      std::vector<kern::IcWeight> gspec{{alpha0, 2.0, 1, 0, 0}};
       for (size_t gi = 0; gi < gammas.size(); ++gi) {
-        kern::PngProducts pp{};
-        pp.out = r0;
+        kern::PngProducts& pp = zp.pp[gi];
         for (int t = 0; t < png->n_terms; ++t) {
           if (png->terms[t].g != gammas[gi]) continue;
           pp.fa[pp.n] = field(png->terms[t].a);
@@ -1571,36 +1676,67 @@ lpc_status init_ic_impl(const lpc_geometry* geom, const lpc_cosmology* cosmo, ui
           pp.c[pp.n] = static_cast<float>(png->terms[t].c);
           ++pp.n;
         }
-        stage("png products", s, [&] { return kern::png_products(pp, n, s); });
-        run_r2c(jp, prod_r2c[gi], false, flags, s);
-        stage("png power", s, [&] {
-          return kern::png_power(spec, nlhat, N, pitch, geom->box, gammas[gi] * tilt, 1.0, gi > 0, s);
-        });
+        zp.out[gi] = png_mesh[gi];
+        gspec.push_back({alpha0 * png->f_nl, 2.0 + gammas[gi] * tilt, 1, 0, 0});
       }
-      stage("png to delta", s, [&] {
-        return kern::png_to_delta(dhat, nlhat, N, pitch, geom->box, png->f_nl, alpha0, c.omega_m, c.h, s);
-      });
+      stage("ic products", s, [&] { return kern::ic_r2c(zp, false, static_cast<int>(gammas.size()), s); });
+      run_y(y_groups, false);
+      const double* wg = weights(D, gspec);
+      xd.base = A;
+      xd.wbase = wg;
+      xd.nin = static_cast<int>(gammas.size());
+      for (int i = 0; i < xd.nin; ++i) {
+        xd.in[i] = png_mesh[i];
+        xd.w[i] = wg + static_cast<size_t>(i + 1) * n2_count;
+      }
     }
-    for (int k = 0; k < 3; ++k) derived(k);  // Psi1
-    for (int k = 3; k < 6; ++k) derived(k);  // phi_xx, phi_yy, phi_zz
-    stage("source", s, [&] { return kern::ic_source_init(r0, r1, r2, n, s); });
-    for (int k = 6; k < 9; ++k) {            // phi_xy, phi_xz, phi_yz
-      derived(k);
-      stage("source", s, [&] { return kern::ic_sub_square(r0, r1, n, s); });
+    xd.nout = 3;
+    float2* xout[3] = {A, B, C};
+    for (int o = 0; o < 3; ++o) {
+      xd.out[o] = xout[o];
+      xd.kind[o] = 2 - o;  // kx^2 phi, i kx phi, phi
     }
-    run_r2c(jp, source, false, flags, s);    // source spectrum replaces delta_hat
-    // Psi2 = i k phi2_hat; kinds 9..11 read the source spectrum in dhat
-    for (int j = 0; j < 3; ++j) {
-      stage("spectral factor", s, [&] { return kern::ic_spectral_factor(dhat, spec, N, pitch, geom->box, 9 + j, s); });
-      run_c2r(jp, der[9 + j], s);
-    }
+    stage("ic x", s, [&] { return kern::ic_x(xd, s); });
+    kern::IcY yd{};
+    yd.N = N;
+    yd.pitch = pitch;
+    yd.kf = static_cast<float>(kf);
+    yd.tw = tw;
+    yd.pl = full;
+    for (int o = 0; o < 3; ++o) yd.in[o] = yd.out[o][0] = xout[o];
+    yd.out[1][1] = P;  // xy
+    yd.out[2][1] = V;  // y
+    yd.out[2][2] = D;  // yy
+    stage("ic y first", s, [&] { return kern::ic_y(yd, s); });
+    const float2* zin[6] = {A, B, P, C, V, D};
+    kern::IcZ z1 = zi;
+    std::copy(zin, zin + 6, z1.in);
+    z1.source = A;
+    stage("ic z first", s, [&] { return kern::ic_z(z1, kern::kIcFirst, 1, s); });
+    // Psi2 = grad phi2, lap phi2 = source: -source / k^2 and its gradient as in the force
+    run_y(y_noise, false);
+    kern::IcX x2 = x0;
+    x2.sign = -1.f;
+    x2.nin = 1;
+    x2.in[0] = A;
+    x2.nout = 2;
+    x2.out[0] = A;
+    x2.kind[0] = 1;
+    x2.out[1] = C;
+    x2.kind[1] = 0;
+    stage("ic x", s, [&] { return kern::ic_x(x2, s); });
+    stage("ic y inv", s, [&] { return kern::launch_y_grad(jp.jobs<kern::YGradJob>(y_psi2), jp.table(y_psi2), Bax, Pax, lds_ax, s); });
     const double d1 = host::growth_D1(c, a_init), d2 = host::growth_D2(c, a_init);
     const double E = host::hubble_E(c, a_init), a3 = a_init * a_init * a_init;
-    const double f1 = a3 * E * host::growth_dD1(c, a_init), f2 = a3 * E * host::growth_dD2(c, a_init);
-    stage("assemble", s, [&] {
-      return kern::ic_assemble(out->pos, out->vel, out->id, out->psi1, out->psi2, N, geom->box, static_cast<float>(d1),
-                               static_cast<float>(d2), static_cast<float>(f1), static_cast<float>(f2), s);
-    });
+    kern::IcZ z2 = zi;
+    z2.in[0] = A;
+    z2.in[1] = B;
+    z2.in[2] = C;
+    z2.d1 = static_cast<float>(d1);
+    z2.d2 = static_cast<float>(d2);
+    z2.f1 = static_cast<float>(a3 * E * host::growth_dD1(c, a_init));
+    z2.f2 = static_cast<float>(a3 * E * host::growth_dD2(c, a_init));
+    stage("ic z second", s, [&] { return kern::ic_z(z2, kern::kIcSecond, 1, s); });
     return finish(flags, s);
   });
 }

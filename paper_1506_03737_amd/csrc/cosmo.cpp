@@ -62,6 +62,14 @@ double integrate(F f, double lo, double hi, int pieces = 1) {
 
 }  // namespace
 
+void gauss_legendre64(double* x, double* w) {
+  const GaussLegendre& g = gl64();
+  for (int i = 0; i < 64; ++i) {
+    x[i] = g.x[static_cast<size_t>(i)];
+    w[i] = g.w[static_cast<size_t>(i)];
+  }
+}
+
 double hubble_E(const Cosmo& c, double a) { return std::sqrt(c.omega_m / (a * a * a) + (1.0 - c.omega_m)); }
 
 // int_0^a da' / (a' E(a'))^3 with a' = t^2: the integrand 2 t^4 (Om + OL t^6)^(-3/2) is smooth at t = 0.

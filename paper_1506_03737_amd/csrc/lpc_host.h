@@ -31,6 +31,8 @@ double comoving_distance(const Cosmo& c, double a);
 double growth_suppression(const Cosmo& c);
 void coefficient_table(const Cosmo& c, bool modified, double n_lpt, const double* a, int n, double* out);
 double pk_amplitude(const Cosmo& c);
+// The 64 Gauss-Legendre nodes on [-1, 1] and their weights.
+void gauss_legendre64(double* x, double* w);
 double linear_pk(const Cosmo& c, double amplitude, double k);
 
 }  // namespace host

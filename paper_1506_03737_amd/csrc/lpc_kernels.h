@@ -308,35 +308,90 @@ hipError_t launch_poisson(const PoissonJob* jobs, WorkTable wt, int B, int M, bo
 bool poisson_chainable(const Plan1D& pl);
 hipError_t launch_z_c2r(const ZC2RJob* jobs, WorkTable wt, int nc, int R, int P, size_t lds, hipStream_t s);
 
-// Initial conditions on an N^3 lattice.
-hipError_t ic_noise(uint64_t seed, int N, float* out, hipStream_t s);
-// delta_hat = noise_hat * sqrt(P(k) N^3 / V) in place (half spectrum, pitch); zero k = 0 and Nyquist planes.
-hipError_t ic_scale_spectrum(float2* spec, int N, int pitch, double box, double amplitude, double omega_m, double h,
-                             double n_s, hipStream_t s);
-// out = factor * in with factor one of: kind 0..2 -> i k_j / k^2 (Psi1_j), kind 3..8 -> k_i k_j / k^2 (phi1_ij for
-// (xx, yy, zz, xy, xz, yz)), kind 9..11 -> -i k_j / k^2 (Psi2_j from the source spectrum); zero at k = 0 / Nyquist.
-hipError_t ic_spectral_factor(const float2* in, float2* out, int N, int pitch, double box, int kind, hipStream_t s);
-// S = a*b + a*c + b*c (written into a), then S -= d^2 via ic_sub_square
-hipError_t ic_source_init(float* a, const float* b, const float* c, int64_t count, hipStream_t s);
-hipError_t ic_sub_square(float* S, const float* d, int64_t count, hipStream_t s);
-// Primordial non-Gaussianity (Sec. 5): phi_hat from the noise spectrum; D^s spectral multipliers; the real-space sum
-// of the products of a group of terms; delta_L_hat = alpha0 k^2 T(k) (phi_hat + fNL NL_hat).
+// Initial conditions on an N^3 lattice (ic.hip). All spectra are half spectra of the mesh layout whose kz = N / 2 column is
+// neither read nor written (every Nyquist mode of the fields is zero).
+// sigma(8)^2 of the spectrum k^ns T^2 as kIcPieces partial integrals; gl: 64 Gauss-Legendre nodes, then their weights.
+constexpr int kIcPieces = 400;
+hipError_t ic_sigma8(const double* gl, double n_s, double om_h, double* parts, hipStream_t s);
+// Spectral weight tables: table[t][n2] = coef k^expo T(k)^transfer (times the linear spectrum's amplitude with
+// `amplitude`; the square root of it all with `root`), k = kf sqrt(n2), for the integer n2 < count of a mode; 0 at n2 = 0.
+constexpr int kIcMaxWeights = 6;
+struct IcWeight {
+  double coef, expo;
+  int transfer, amplitude, root;
+};
+struct IcWeights {
+  double* table;
+  const double* sigma8_parts;
+  int count;
+  double kf, om_h, sigma8;
+  IcWeight spec[kIcMaxWeights];
+};
+hipError_t ic_weights(const IcWeights& w, int tables, hipStream_t s);
+// Primordial non-Gaussianity (Sec. 5): the real-space sum of the products of a group of terms.
 constexpr int kPngMaxTerms = 4;
-struct PngProducts {  // out[i] = sum_t c[t] fa[t][i] fb[t][i]
-  float* out;
+struct PngProducts {  // sum_t c[t] fa[t][i] fb[t][i]
   const float* fa[kPngMaxTerms];
   const float* fb[kPngMaxTerms];
   float c[kPngMaxTerms];
   int n;
 };
-hipError_t png_potential(float2* spec, int N, int pitch, double box, double a_phi, double n_s, hipStream_t s);
-hipError_t png_power(const float2* in, float2* out, int N, int pitch, double box, double expo, double coef,
-                     bool accumulate, hipStream_t s);
-hipError_t png_products(const PngProducts& pp, int64_t count, hipStream_t s);
-hipError_t png_to_delta(float2* phi, const float2* nl, int N, int pitch, double box, double f_nl, double alpha0,
-                        double omega_m, double h, hipStream_t s);
-hipError_t ic_assemble(float* pos, float* vel, int32_t* id, const float* psi1, const float* psi2, int N, double box,
-                       float d1, float d2, float f1, float f2, hipStream_t s);
+// Forward z pass of the white noise (one mesh) or of each group's products.
+struct IcR2C {
+  float2* out[kPngMaxTerms];
+  const float2 *tw, *roots;  // of the length N / 2 plan and the real split
+  Plan1D pl;
+  int N, pitch;
+  uint64_t seed;
+  PngProducts pp[kPngMaxTerms];
+};
+hipError_t ic_r2c(const IcR2C& a, bool noise, int groups, hipStream_t s);
+// x pass: delta = wbase base + sum_i w_i FFT_x(in_i) (a NULL weight: 1; base NULL: none), stored to keep if not NULL; out[o] = the
+// inverse x transform of wout[o] delta, or (wout[o] NULL) of sign / k^2 times delta (kind 0), i kx delta (1) or
+// kx^2 delta (2). Weights are indexed by |n|^2. Any buffer may be an input and an output.
+struct IcX {
+  const float2* in[kPngMaxTerms];
+  const double* w[kPngMaxTerms];
+  const float2* base;
+  const double* wbase;
+  float2* keep;
+  float2* out[3];
+  const double* wout[3];
+  int kind[3];
+  int nin, nout, N, pitch, ntc;
+  float kf, sign;
+  const float2* tw;
+  Plan1D pl;
+};
+hipError_t ic_x(IcX a, hipStream_t s);
+// y pass of the first-order fields: in[kind] (kx^2 phi, i kx phi, phi) to out[kind][0..kind] (see k_ic_y).
+struct IcY {
+  const float2* in[3];
+  float2* out[3][3];
+  int N, pitch, ntc;
+  float kf;
+  const float2* tw;
+  Plan1D pl;
+};
+hipError_t ic_y(IcY a, hipStream_t s);
+// z pass (see k_ic_z). kIcFirst: in = xx, x, xy, 1, y, yy -> psi1 and the source's forward z transform; kIcSecond: in = the
+// Psi2 spectra with the last one's i kz still to apply -> psi2, pos, vel, id; kIcPlain: in[f] -> real[f], f < fields.
+enum { kIcFirst = 0, kIcSecond = 1, kIcPlain = 2 };
+struct IcZ {
+  const float2* in[6];
+  float2* source;
+  float *psi1, *psi2, *pos, *vel;
+  int32_t* id;
+  float* real[3];
+  const float2 *tw, *roots;
+  Plan1D pl;
+  int N, pitch, R;
+  bool aligned;  // the output arrays are 8-byte aligned
+  float kf, scale;
+  double box;
+  float d1, d2, f1, f2;
+};
+hipError_t ic_z(const IcZ& a, int mode, int fields, hipStream_t s);
 
 // Power-spectrum binning of a half spectrum: sums[b] += (k, P) per mode, counts[b] += multiplicity.
 // Reduced-bispectrum pieces (FFT shell estimator). A shell is klo <= |k| < khi. shell_fill writes a whole half
