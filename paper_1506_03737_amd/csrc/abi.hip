@@ -1872,53 +1872,131 @@ lpc_status lpc_bispectrum(const lpc_geometry* geom, const float* pos, int64_t n,
   return guarded([&]() {
     const int nm = geom->n_mesh, pitch = kern::mesh_pitch(nm);
     const int64_t M = static_cast<int64_t>(nm) * nm * nm;
-    const double box = geom->box;
+    const double box = geom->box, kf = 2.0 * M_PI / box;
     int* flags = reinterpret_cast<int*>(ws);
     float2* A = reinterpret_cast<float2*>(at(ws, p.A));
-    float2* H = reinterpret_cast<float2*>(at(ws, p.B));
-    float* F[3];
-    for (int i = 0; i < 3; ++i) F[i] = reinterpret_cast<float*>(at(ws, p.fields)) + i * M;
     double* parts = reinterpret_cast<double*>(at(ws, p.bins));
     const int nb = kern::sum_blocks();
     JobPack jp(at(ws, p.jobs));
     const DensitySpectrum ds = add_density_spectrum(jp, ws, p, geom, pos, n, LPC_OP_BISPECTRUM, A);
-    // the unnormalised inverse transform of H into each of the three real meshes (H is consumed each time)
-    const C2RSections inv[3] = {add_c2r(jp, H, nm, F[0], 1.f), add_c2r(jp, H, nm, F[1], 1.f),
-                                add_c2r(jp, H, nm, F[2], 1.f)};
+    // Distinct shells, by the integer |n|^2 of their modes: the smallest n2 with kf sqrt(n2) >= k (the FP64 operations of
+    // the shell's definition, so the same modes).
+    const int64_t n2_end = 3 * static_cast<int64_t>(nm / 2) * (nm / 2) + 1;
+    auto first_n2 = [&](double k) {
+      const double q = std::max(0.0, k / kf);
+      if (q * q > static_cast<double>(n2_end)) return n2_end;
+      int64_t v = std::max<int64_t>(0, static_cast<int64_t>(q * q) - 2);
+      while (v < n2_end && !(kf * std::sqrt(static_cast<double>(v)) >= k)) ++v;
+      while (v > 0 && kf * std::sqrt(static_cast<double>(v - 1)) >= k) --v;
+      return v;
+    };
+    std::map<double, int> shell_of;
+    std::vector<kern::ShellPower> shells;
+    std::vector<int> shell_id(static_cast<size_t>(3) * m);
+    for (int t = 0; t < 3 * m; ++t) {
+      const auto it = shell_of.emplace(k123[t], static_cast<int>(shells.size()));
+      if (it.second) {
+        kern::ShellPower q{};
+        q.n2lo = static_cast<int>(first_n2(k123[t] - 0.5 * dk));
+        q.n2hi = static_cast<int>(first_n2(k123[t] + 0.5 * dk));
+        while (static_cast<int64_t>(q.nmax + 1) * (q.nmax + 1) < q.n2hi) ++q.nmax;
+        // a shell's partial sums take the place of its first triangle corner's
+        q.parts = parts + (static_cast<size_t>(t / 3) * kPartsPerTriangle + 2 + 2 * (t % 3)) * nb;
+        shells.push_back(q);
+      }
+      shell_id[static_cast<size_t>(t)] = it.first->second;
+    }
+    // Meshes for the fields: everything but delta_hat and the partial sums is free once delta_hat is there.
+    const size_t cbytes = round_up(static_cast<size_t>(nm) * nm * pitch * sizeof(float2));
+    std::vector<float2*> meshes;
+    for (const auto& r : {std::pair<size_t, size_t>{p.dens, p.A}, {p.B, p.bins}, {p.sort, p.total}})
+      for (size_t off = r.first; off + cbytes <= r.second && meshes.size() < 64; off += cbytes)
+        meshes.push_back(reinterpret_cast<float2*>(at(ws, off)));
+    // Groups of (triangle, filter) products whose fields fit the meshes (at least three at every size).
+    struct Group {
+      std::vector<kern::ShellField> fields;
+      std::vector<kern::ShellTriple> triples;
+      const kern::ShellField* fields_dev;
+      const kern::ShellTriple* triples_dev;
+    };
+    std::vector<Group> groups(1);
+    std::map<int, int> have;  // 2 shell + indicator -> field of the open group
+    for (int t = 0; t < m; ++t) {
+      for (int ind = 0; ind < 2; ++ind) {
+        int want[3], fresh = 0;
+        for (int i = 0; i < 3; ++i) {
+          want[i] = 2 * shell_id[static_cast<size_t>(3 * t + i)] + ind;
+          bool seen = have.count(want[i]) != 0;
+          for (int j = 0; j < i; ++j) seen = seen || want[j] == want[i];
+          fresh += seen ? 0 : 1;
+        }
+        if (groups.back().fields.size() + static_cast<size_t>(fresh) > meshes.size()) {
+          groups.emplace_back();
+          have.clear();
+        }
+        Group& g = groups.back();
+        kern::ShellTriple q{};
+        for (int i = 0; i < 3; ++i) {
+          const auto it = have.emplace(want[i], static_cast<int>(g.fields.size()));
+          if (it.second) {
+            const kern::ShellPower& sh = shells[static_cast<size_t>(want[i] / 2)];
+            g.fields.push_back({meshes[g.fields.size()], sh.n2lo, sh.n2hi, sh.nmax, ind});
+          }
+          int c = 0;
+          while (c < q.nc && q.field[c] != it.first->second) ++c;
+          if (c == q.nc) q.field[q.nc++] = it.first->second;
+          q.column[i] = c;
+        }
+        q.parts = parts + (static_cast<size_t>(t) * kPartsPerTriangle + ind) * nb;
+        g.triples.push_back(q);
+      }
+    }
+    kern::ShellPasses sp{};
+    sp.spec = A;
+    sp.n = nm;
+    sp.pitch = pitch;
+    sp.pl = plan_of(nm);
+    sp.plh = plan_of(nm / 2);
+    sp.tw = jp.twiddles(sp.pl);
+    sp.twh = jp.twiddles(sp.plh);
+    sp.roots = jp.half_roots(nm);
+    std::vector<double> win(static_cast<size_t>(nm / 2 + 1), 1.0);
+    for (int i = 1; i <= nm / 2; ++i) {
+      const double x = M_PI * static_cast<double>(i) / nm, v = std::sin(x) / x;
+      win[static_cast<size_t>(i)] = v * v;
+    }
+    sp.win = static_cast<const double*>(jp.data(win.data(), win.size() * sizeof(double)));
+    const auto* shells_dev = static_cast<const kern::ShellPower*>(jp.data(shells.data(), shells.size() * sizeof(shells[0])));
+    for (Group& g : groups) {
+      g.fields_dev = static_cast<const kern::ShellField*>(jp.data(g.fields.data(), g.fields.size() * sizeof(g.fields[0])));
+      g.triples_dev =
+          static_cast<const kern::ShellTriple*>(jp.data(g.triples.data(), g.triples.size() * sizeof(g.triples[0])));
+    }
+    std::vector<double> sums(static_cast<size_t>(m) * kPartsPerTriangle, 0.0);
+    double* sums_dev = static_cast<double*>(const_cast<void*>(jp.data(sums.data(), sums.size() * sizeof(double))));
     jp.upload(s);
     stage("clear", s, [&] { return kern::clear_call(flags, ds.ss.cnt, ds.ss.G, s); });
     run_density_spectrum(jp, ds, flags, s);
-    for (int t = 0; t < m; ++t) {
-      double* pt = parts + static_cast<size_t>(t) * kPartsPerTriangle * nb;
-      for (int ind = 0; ind < 2; ++ind) {  // shell-filtered fields, then the shell indicators
-        for (int i = 0; i < 3; ++i) {
-          const double kc = k123[3 * t + i];
-          stage("shell fill", s, [&] {
-            return kern::shell_fill(A, H, nm, pitch, box, kc - 0.5 * dk, kc + 0.5 * dk, ind == 1, s);
-          });
-          run_c2r(jp, inv[i], s);
-        }
-        stage("triple sum", s, [&] { return kern::triple_sum(F[0], F[1], F[2], M, pt + ind * nb, s); });
-      }
-      for (int i = 0; i < 3; ++i) {
-        const double kc = k123[3 * t + i];
-        stage("shell power", s, [&] {
-          return kern::shell_power(A, nm, pitch, box, kc - 0.5 * dk, kc + 0.5 * dk, pt + (2 + 2 * i) * nb,
-                                   pt + (3 + 2 * i) * nb, s);
-        });
-      }
-    }
-    std::vector<double> hp(static_cast<size_t>(m) * kPartsPerTriangle * nb);
-    check(hipMemcpyAsync(hp.data(), parts, hp.size() * sizeof(double), hipMemcpyDeviceToHost, s), "copy sums");
+    stage("shell power", s, [&] { return kern::shell_power(sp, shells_dev, static_cast<int>(shells.size()), s); });
+    for (const Group& g : groups)
+      stage("shell fields", s, [&] {
+        return kern::shell_fields(sp, g.fields_dev, static_cast<int>(g.fields.size()), g.triples_dev,
+                                  static_cast<int>(g.triples.size()), s);
+      });
+    stage("sum parts", s, [&] { return kern::sum_parts(parts, m * kPartsPerTriangle, sums_dev, s); });
+    check(hipMemcpyAsync(sums.data(), sums_dev, sums.size() * sizeof(double), hipMemcpyDeviceToHost, s), "copy sums");
     lpc_status st = finish(flags, s);
     if (st != LPC_OK) return st;
     const double V = box * box * box, Md = static_cast<double>(M);
     for (int t = 0; t < m; ++t) {
-      double sum[kPartsPerTriangle] = {};
-      for (int q = 0; q < kPartsPerTriangle; ++q)
-        for (int b = 0; b < nb; ++b) sum[q] += hp[(static_cast<size_t>(t) * kPartsPerTriangle + q) * nb + b];
+      const double* sum = sums.data() + static_cast<size_t>(t) * kPartsPerTriangle;
       double pw[3];
-      for (int i = 0; i < 3; ++i) pw[i] = (sum[3 + 2 * i] > 0.0) ? V / (Md * Md) * sum[2 + 2 * i] / sum[3 + 2 * i] : std::nan("");
+      for (int i = 0; i < 3; ++i) {
+        // the corner's shell, whose sums sit at the first corner that has it
+        const kern::ShellPower& sh = shells[static_cast<size_t>(shell_id[static_cast<size_t>(3 * t + i)])];
+        const double* q = sums.data() + (sh.parts - parts) / nb;
+        pw[i] = (q[1] > 0.0) ? V / (Md * Md) * q[0] / q[1] : std::nan("");
+      }
       // sum_x I1 I2 I3 is Nm^3 times the number of closed triangles (exact up to FP32 rounding of the fields)
       B[t] = (sum[1] >= 0.5 * Md) ? V * V / (Md * Md * Md) * sum[0] / sum[1] : std::nan("");
       Q[t] = B[t] / (pw[0] * pw[1] + pw[1] * pw[2] + pw[2] * pw[0]);

@@ -393,17 +393,36 @@ struct IcZ {
 };
 hipError_t ic_z(const IcZ& a, int mode, int fields, hipStream_t s);
 
-// Power-spectrum binning of a half spectrum: sums[b] += (k, P) per mode, counts[b] += multiplicity.
-// Reduced-bispectrum pieces (FFT shell estimator). A shell is klo <= |k| < khi. shell_fill writes a whole half
-// spectrum (pitch included): delta_hat / W in the shell (or 1 with indicator), 0 elsewhere. triple_sum and
-// shell_power write sum_blocks() FP64 partial sums each: sum a b c over M cells; sum of mult |delta_hat|^2 / W^2 and
-// of mult over the shell's modes (mult 2 off the kz = 0 and Nyquist planes).
-hipError_t shell_fill(const float2* spec, float2* out, int nm, int pitch, double box, double klo, double khi,
-                      bool indicator, hipStream_t s);
-hipError_t triple_sum(const float* a, const float* b, const float* c, int64_t M, double* part, hipStream_t s);
-hipError_t shell_power(const float2* spec, int nm, int pitch, double box, double klo, double khi, double* part_p,
-                       double* part_n, hipStream_t s);
+// Reduced-bispectrum pieces (FFT shell estimator; pk.hip). A shell is the modes n2lo <= |n|^2 < n2hi, all with
+// |n_d| <= nmax. A field is a shell's delta_hat / W (or 1 with indicator) and the mesh of its inverse transform; a triple
+// names nc <= 3 distinct fields and which of them (column) each of its three factors is.
+struct ShellField {
+  float2* mesh;
+  int n2lo, n2hi, nmax, indicator;
+};
+struct ShellTriple {
+  int nc, field[3], column[3];
+  double* parts;   // sum_blocks() partial sums of the product over the mesh
+};
+struct ShellPower {
+  int n2lo, n2hi, nmax;
+  double* parts;   // 2 sum_blocks(): sum of mult |delta_hat|^2 / W^2, then of mult (2 off the kz = 0 and Nyquist planes)
+};
+struct ShellPasses {
+  const float2* spec;        // delta_hat
+  const double* win;         // CIC window sinc^2(pi m / n), m <= n / 2
+  const float2 *tw, *twh, *roots;
+  Plan1D pl, plh;            // lengths n and n / 2
+  int n, pitch, ntc, R;
+};
+// The inverse transforms of the fields and the product sums of the triples over them.
+hipError_t shell_fields(ShellPasses a, const ShellField* fields, int nfield, const ShellTriple* triples, int ntriple,
+                        hipStream_t s);
+hipError_t shell_power(const ShellPasses& a, const ShellPower* shells, int nshell, hipStream_t s);
+// out[r] = the sum of parts[r][0 .. sum_blocks()) in a fixed order
+hipError_t sum_parts(const double* parts, int rows, double* out, hipStream_t s);
 int sum_blocks();
+// Power-spectrum binning of a half spectrum: sums[b] += (k, P) per mode, counts[b] += multiplicity.
 hipError_t pk_bin(const float2* spec, int nm, int pitch, double box, double k_max, int n_bins, double pscale,
                   double* sums, unsigned long long* counts, hipStream_t s);
 
