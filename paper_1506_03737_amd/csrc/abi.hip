@@ -594,7 +594,45 @@ struct ForceProgram {
   SortSpace ss;
   bool cola_run = false;
   bool fixed_in = false;  // the deposit writes int64 counts for the forward transform (else the FP32 contrast)
+  int* split_count = nullptr;  // a single box whose heavy tiles the deposit may split
 };
+
+// Particles of a box from which its heaviest tiles may be split: below, no tile can hold so many that the launch of the
+// chunks' kernel (5 us) would be won back.
+constexpr int64_t kSplitMin = 1 << 17;
+
+// Slots and list for splitting the heavy tiles of a box of n particles in the spare bytes [base, base + bytes) (free from
+// before the scatter until after the deposit).
+kern::DepSplit dep_split(char* base, size_t bytes, const kern::TileGrid& nt, int64_t n) {
+  kern::DepSplit sp{};
+  sp.trigger = INT32_MAX;
+  if (n < kSplitMin) return sp;
+  // the list takes an eighth of the space, the slots (with their arrival counts) what is left
+  const size_t entries = bytes / 8 / sizeof(int2);
+  const size_t head = round_up(2 * sizeof(int)) + round_up(sizeof(int) * static_cast<size_t>(nt.count())) +
+                      round_up(sizeof(int2) * entries) + 2 * kAlign;
+  const size_t per_slot = kern::dep_split_slot_bytes() + sizeof(int);
+  if (entries < 2 || bytes < head + per_slot) return sp;
+  const size_t slots = (bytes - head) / per_slot;
+  char* at = base;
+  auto take = [&at](size_t b) {
+    char* p = at;
+    at += round_up(b);
+    return p;
+  };
+  sp.count = reinterpret_cast<int*>(take(2 * sizeof(int)));
+  sp.marker = reinterpret_cast<int*>(take(sizeof(int) * static_cast<size_t>(nt.count())));
+  sp.list = reinterpret_cast<int2*>(take(sizeof(int2) * entries));
+  sp.arrive = reinterpret_cast<int*>(take(sizeof(int) * slots));
+  sp.sums = reinterpret_cast<unsigned long long*>(at);
+  sp.slots = static_cast<int>(std::min<size_t>(slots, 1 << 20));
+  sp.entries = static_cast<int>(std::min<size_t>(entries, 1 << 28));
+  // Chunks of 4096 particles (16 per thread). The chunks' kernel runs before the whole tiles', so a tile is split only when
+  // it would outlast them: four times the mean (a uniform tile is reached by 1.4 times its own particles), 8192 at least.
+  sp.size = 4096;
+  sp.trigger = static_cast<int>(std::min<int64_t>(INT32_MAX, std::max<int64_t>(8192, 4 * n / nt.count())));
+  return sp;
+}
 
 ForceProgram add_force(JobPack& jp, const std::vector<ForceBox>& boxes, const SortSpace& ss, int deconv,
                        bool cola_run) {
@@ -686,6 +724,12 @@ ForceProgram add_force(JobPack& jp, const std::vector<ForceBox>& boxes, const So
       d.mscale = (static_cast<double>(M) / static_cast<double>(b.n)) * 0x1.0p-48;
       d.dens = f.fixed_in ? b.dens : nullptr;
       d.delta = f.fixed_in ? nullptr : b.force;  // the contrast takes the start of the density / force region
+      // the rest of that region is free until the force mesh is written
+      const size_t used = round_up(static_cast<size_t>(M) * sizeof(float));
+      d.split.trigger = INT32_MAX;
+      if (boxes.size() == 1)
+        d.split = dep_split(reinterpret_cast<char*>(b.force) + used, static_cast<size_t>(M) * 12 - used, nt, b.n);
+      f.split_count = d.split.count;
       dj[c].push_back(d);
       kern::PartJob p{};
       p.pos = cp.pos;
@@ -804,23 +848,26 @@ ForceProgram add_force(JobPack& jp, const std::vector<ForceBox>& boxes, const So
 // Tile sort of every box. The bucket counts are zero when it begins: clear_call zeroes them at the start of a call (before
 // the graph of a batched run), the scan leaves them zeroed for the next key pass.
 // keys_done: the key pass already ran (folded into the previous drift), so only the scan and the scatter remain
-void run_sort(const JobPack& jp, const SortSpace& ss, const Section& sec, int* flags, hipStream_t s,
-              bool keys_done = false) {
+// dep: the deposit jobs of a single box, whose heavy tiles are marked on the way when split_count is set
+void run_sort(const JobPack& jp, const SortSpace& ss, const Section& sec, const Section& dep, int* split_count, int* flags,
+              hipStream_t s, bool keys_done = false) {
   if (!keys_done) {
     stage("sort keys", s, [&] {
       return kern::launch_tile_key(jp.jobs<kern::SortJob>(sec), jp.table(sec), ss.cnt, ss.key, ss.rank, flags, s);
     });
   }
-  stage("sort scan", s, [&] { return kern::launch_scan(ss.cnt, ss.start, ss.G, ss.block_sums, s); });
+  stage("sort scan", s, [&] { return kern::launch_scan(ss.cnt, ss.start, ss.G, ss.block_sums, split_count, s); });
   stage("sort scatter", s, [&] {
-    return kern::launch_scatter(jp.jobs<kern::SortJob>(sec), jp.table(sec), ss.key, ss.rank, ss.start, s);
+    return kern::launch_scatter(jp.jobs<kern::SortJob>(sec), jp.table(sec), ss.key, ss.rank, ss.start,
+                                split_count ? jp.jobs<kern::DepJob>(dep) : nullptr, s);
   });
 }
 
 // deposit (from sorted copy c) -> delta -> forward FFT -> Poisson/gradient -> inverse FFTs -> AoS force meshes
 void run_force_mesh(const JobPack& jp, const ForceProgram& f, int c, int* flags, hipStream_t s) {
   stage("deposit", s, [&] {
-    return kern::launch_deposit_tiles(jp.jobs<kern::DepJob>(f.dep[c]), jp.table(f.dep[c]), f.ss.start, flags, s);
+    return kern::launch_deposit_tiles(jp.jobs<kern::DepJob>(f.dep[c]), jp.table(f.dep[c]), f.ss.start,
+                                      f.split_count != nullptr, flags, s);
   });
   stage("fft z r2c", s, [&] {
     return kern::launch_z_r2c(jp.jobs<kern::ZR2CJob>(f.zr2c), jp.table(f.zr2c), f.fixed_in, f.Bz, f.Pz, f.lds_z, flags,
@@ -840,14 +887,14 @@ void run_cola(const JobPack& jp, const ForceProgram& f, const std::vector<double
               int* flags, hipStream_t s, const std::vector<kern::LightconeStep>* lc = nullptr) {
   auto row = [&tab](int i) { return tab.data() + static_cast<size_t>(i) * host::kCoefColumns; };
   int c = 0;
-  run_sort(jp, f.ss, f.sort_user, flags, s);
+  run_sort(jp, f.ss, f.sort_user, f.dep[0], f.split_count, flags, s);
   if (cola) {
     const float f1 = static_cast<float>(-row(0)[host::kF1]), f2 = static_cast<float>(-row(0)[host::kF2]);
     stage("frame velocity", s, [&] { return kern::launch_frame(jp.jobs<kern::PartJob>(f.frame[c]), jp.table(f.frame[c]), f1, f2, s); });
   }
   for (int i = 0; i < n_a; ++i) {
     if (i > 0) {
-      run_sort(jp, f.ss, f.sort_next[c], flags, s, true);
+      run_sort(jp, f.ss, f.sort_next[c], f.dep[1 - c], f.split_count, flags, s, true);
       c = 1 - c;
     }
     const double* r = row(i);
@@ -953,7 +1000,7 @@ lpc_status pm_force_impl(const lpc_geometry* geom, const lpc_stepping* step, con
                                      false);
     jp.upload(s);
     stage("clear", s, [&] { return kern::clear_call(flags, f.ss.cnt, f.ss.G, s); });
-    run_sort(jp, f.ss, f.sort_user, flags, s);
+    run_sort(jp, f.ss, f.sort_user, f.dep[0], f.split_count, flags, s);
     run_force_mesh(jp, f, 0, flags, s);
     stage("gather", s, [&] { return kern::launch_gather(jp.jobs<kern::PartJob>(f.parts[0]), jp.table(f.parts[0]), flags, s); });
     return finish(flags, s);
@@ -1751,6 +1798,7 @@ struct DensitySpectrum {
   SortSpace ss;
   Section sort, dep;
   R2CSections r;
+  int* split_count = nullptr;
 };
 
 DensitySpectrum add_density_spectrum(JobPack& jp, void* ws, const Plan& p, const lpc_geometry* geom, const float* pos,
@@ -1783,15 +1831,19 @@ DensitySpectrum add_density_spectrum(JobPack& jp, void* ws, const Plan& p, const
   dj.scale = sj.scale;
   dj.delta = reinterpret_cast<float*>(at(ws, p.dens));  // the FP32 contrast, in the density region
   dj.mscale = (static_cast<double>(M) / static_cast<double>(n)) * 0x1.0p-48;
+  const size_t used = round_up(static_cast<size_t>(M) * sizeof(float));
+  dj.split = dep_split(at(ws, p.dens) + used, static_cast<size_t>(M) * 8 - used, nt, n);
+  d.split_count = dj.split.count;
   d.dep = jp.add1(dj, nt.count());
   d.r = add_r2c(jp, dj.delta, false, 0.0, nm, A);
   return d;
 }
 
 void run_density_spectrum(const JobPack& jp, const DensitySpectrum& d, int* flags, hipStream_t s) {
-  run_sort(jp, d.ss, d.sort, flags, s);
+  run_sort(jp, d.ss, d.sort, d.dep, d.split_count, flags, s);
   stage("deposit", s, [&] {
-    return kern::launch_deposit_tiles(jp.jobs<kern::DepJob>(d.dep), jp.table(d.dep), d.ss.start, flags, s);
+    return kern::launch_deposit_tiles(jp.jobs<kern::DepJob>(d.dep), jp.table(d.dep), d.ss.start,
+                                      d.split_count != nullptr, flags, s);
   });
   run_r2c(jp, d.r, false, flags, s);
 }

@@ -177,6 +177,17 @@ inline uint32_t div_inverse(int d) {
   return d <= 1 ? 0u : static_cast<uint32_t>(((uint64_t(1) << 32) + static_cast<uint64_t>(d) - 1) / static_cast<uint64_t>(d));
 }
 
+// Splitting of a box's heaviest tiles over several workgroups of the deposit: a tile reached by more than `trigger`
+// particles is worked on in chunks of `size` (< 2^16) of them, whose counts are summed in one of `slots` slots (no
+// splitting: trigger INT_MAX).
+struct DepSplit {
+  unsigned long long* sums;   // per slot: the tile's counts, and the sums of the chunk counts' high parts
+  int2* list;                 // per chunk: the tile (-1: not used) and the chunk's number in it
+  int* arrive;                // per slot: chunks that have arrived
+  int* marker;                // per tile past the trigger: its slot, or -1
+  int* count;                 // slots and list entries asked for
+  int slots, entries, size, trigger;
+};
 struct DepJob {         // tiled deposit of one box from its tile-sorted positions
   const float* pos;
   int64_t n, pbase;
@@ -187,6 +198,7 @@ struct DepJob {         // tiled deposit of one box from its tile-sorted positio
   uint64_t* dens;       // int64 counts, or NULL
   float* delta;         // FP32 density contrast C mscale - 1, or NULL
   double mscale;
+  DepSplit split;
 };
 struct UnsortJob {      // sorted pos / vel back to the caller's order
   const float* spos;
@@ -279,11 +291,15 @@ size_t lds_z_c2r(int n, int B);
 hipError_t launch_tile_key(const SortJob* jobs, WorkTable wt, int* cnt, int* key, int* rank, int* flags,
                            hipStream_t s);
 int scan_blocks(int count);  // entries of the block-sum scratch of launch_scan
-// start: count + 1 entries; cnt is left zeroed
-hipError_t launch_scan(int* cnt, int* start, int count, int* block_sums, hipStream_t s);
+// start: count + 1 entries; cnt is left zeroed, and zero[0..1] (if not NULL) are zeroed
+hipError_t launch_scan(int* cnt, int* start, int count, int* block_sums, int* zero, hipStream_t s);
+// dep (or NULL): the deposit job of a single box whose heavy tiles are marked for splitting on the way
 hipError_t launch_scatter(const SortJob* jobs, WorkTable wt, const int* key, const int* rank, const int* start,
-                          hipStream_t s);
-hipError_t launch_deposit_tiles(const DepJob* jobs, WorkTable wt, const int* start, int* flags, hipStream_t s);
+                          const DepJob* dep, hipStream_t s);
+// split: the job's heavy tiles have been marked by launch_scatter
+hipError_t launch_deposit_tiles(const DepJob* jobs, WorkTable wt, const int* start, bool split, int* flags,
+                                hipStream_t s);
+size_t dep_split_slot_bytes();
 hipError_t launch_unsort(const UnsortJob* jobs, WorkTable wt, hipStream_t s);
 // With key != NULL the kernel also does the next sort's key pass on the positions it writes (bucket, rank via cnt,
 // which must be zero): the key pass of k_tile_key folded into the drift.

@@ -245,7 +245,8 @@ constexpr int kScanBlock = kNT * kScanPer;
 constexpr int kScanNT = 1024, kScanOnePer = 16;
 constexpr int kScanOne = kScanNT * kScanOnePer;
 
-__global__ __launch_bounds__(kScanNT) void k_scan_one(int* __restrict__ cnt, int* __restrict__ start, int count) {
+__global__ __launch_bounds__(kScanNT) void k_scan_one(int* __restrict__ cnt, int* __restrict__ start, int count,
+                                                      int* __restrict__ zero) {
   __shared__ int waves[kScanNT / 64];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int per = (count + kScanNT - 1) / kScanNT, base = tid * per;  // per <= kScanOnePer (uniform)
@@ -280,7 +281,10 @@ __global__ __launch_bounds__(kScanNT) void k_scan_one(int* __restrict__ cnt, int
     if (k < per && base + k < count) start[base + k] = run;
     run += v[k];
   }
-  if (tid == 0) start[count] = total;
+  if (tid == 0) {
+    start[count] = total;
+    if (zero) zero[0] = zero[1] = 0;
+  }
 }
 
 __device__ __forceinline__ int block_exclusive_scan(int v, int* sh, int* total) {
@@ -327,7 +331,7 @@ __global__ __launch_bounds__(kNT) void k_scan_local(int* __restrict__ cnt, int* 
 
 // One workgroup: exclusive scan of the block totals in place, and start[count] = the grand total.
 __global__ __launch_bounds__(kNT) void k_scan_sums(int* __restrict__ block_sums, int nblocks, int* __restrict__ start,
-                                                   int count) {
+                                                   int count, int* __restrict__ zero) {
   __shared__ int sh[kNT];
   int carry = 0;
   for (int b0 = 0; b0 < nblocks; b0 += kNT) {
@@ -338,7 +342,10 @@ __global__ __launch_bounds__(kNT) void k_scan_sums(int* __restrict__ block_sums,
     if (b < nblocks) block_sums[b] = carry + ex;
     carry += total;
   }
-  if (threadIdx.x == 0) start[count] = carry;
+  if (threadIdx.x == 0) {
+    start[count] = carry;
+    if (zero) zero[0] = zero[1] = 0;
+  }
 }
 
 __global__ __launch_bounds__(kNT) void k_scan_add(int* __restrict__ start, int count,
@@ -347,6 +354,78 @@ __global__ __launch_bounds__(kNT) void k_scan_add(int* __restrict__ start, int c
   const int add = block_sums[blockIdx.x];
   for (int k = threadIdx.x; k < kScanBlock; k += kNT)
     if (base + k < count) start[base + k] += add;
+}
+
+constexpr int kTileCells = kTX * kTY * kTZ;
+
+// Bucket bounds of tile t's workgroup in the deposit: range q in 0..7 is the tile's own two buckets (q = 0) or the boundary
+// bucket of its lower neighbour along the axes of q's bits (4 x, 2 y, 1 z), at sorted positions [b[q], e[q]) of all boxes;
+// use says whether that neighbour is another tile (an axis with one tile has none). The sixteen loads are issued without
+// branches (unused ones name the tile itself), so they go out together.
+struct TileBounds {
+  int b[8], e[8];
+};
+__device__ __forceinline__ bool tile_range_used(int q, int ntx, int nty, int ntz) {
+  return (ntx > 1 || !(q & 4)) && (nty > 1 || !(q & 2)) && (ntz > 1 || !(q & 1));
+}
+__device__ __forceinline__ TileBounds tile_bounds(const int* __restrict__ start, int tbase, int tx, int ty, int tz,
+                                                  int ntx, int nty, int ntz) {
+  TileBounds r;
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    const int dx = (q >> 2) & 1, dy = (q >> 1) & 1, dz = q & 1;
+    const int sx = dx ? (tx == 0 ? ntx - 1 : tx - 1) : tx, sy = dy ? (ty == 0 ? nty - 1 : ty - 1) : ty,
+              sz = dz ? (tz == 0 ? ntz - 1 : tz - 1) : tz;
+    const int g = tbase + 2 * ((sx * nty + sy) * ntz + sz);
+    r.b[q] = start[q == 0 ? g : g + 1];
+    r.e[q] = start[g + 2];
+  }
+  return r;
+}
+
+// Decides which tiles of a box the deposit splits over several workgroups: a tile reached by more than split.trigger
+// particles takes a slot (zeroed here) and one list entry per split.size of its particles, while there are any.
+// marker[t] is the tile's slot, or -1 (set for tiles past the trigger only). Called by the whole grid of the scatter,
+// whose bucket starts are there.
+__device__ void mark_split_tiles(const LPC_CONST DepJob& J, const int* __restrict__ start) {
+  __shared__ int taken[kNT], s_n;
+  const int ntx = J.ntx, nty = J.nty, ntz = J.ntz, T = ntx * nty * ntz;
+  for (int t0 = blockIdx.x * kNT; t0 < T; t0 += gridDim.x * kNT) {
+    if (threadIdx.x == 0) s_n = 0;
+    __syncthreads();
+    const int t = t0 + static_cast<int>(threadIdx.x);
+    int tot = 0;
+    if (t < T) {
+      const int txy = t / ntz, tz = t - txy * ntz, tx = txy / nty, ty = txy - tx * nty;
+      const TileBounds r = tile_bounds(start, J.tbase, tx, ty, tz, ntx, nty, ntz);
+#pragma unroll
+      for (int q = 0; q < 8; ++q) tot += tile_range_used(q, ntx, nty, ntz) ? r.e[q] - r.b[q] : 0;
+    }
+    if (tot > J.split.trigger) {
+      int slot = atomicAdd(J.split.count, 1);
+      if (slot < J.split.slots) {
+        const int chunks = (tot + J.split.size - 1) / J.split.size;
+        const int at = atomicAdd(J.split.count + 1, chunks);
+        if (at + chunks <= J.split.entries) {
+          for (int c = 0; c < chunks; ++c) J.split.list[at + c] = make_int2(t, c);
+          J.split.arrive[slot] = 0;
+          taken[atomicAdd(&s_n, 1)] = slot;
+        } else {
+          for (int c = 0; c < chunks && at + c < J.split.entries; ++c) J.split.list[at + c] = make_int2(-1, 0);
+          slot = -1;
+        }
+      } else {
+        slot = -1;
+      }
+      J.split.marker[t] = slot;
+    }
+    __syncthreads();
+    for (int k = 0; k < s_n; ++k) {
+      unsigned long long* sum = J.split.sums + static_cast<size_t>(taken[k]) * (2 * kTileCells);
+      for (int i = threadIdx.x; i < 2 * kTileCells; i += kNT) sum[i] = 0ull;
+    }
+    __syncthreads();
+  }
 }
 
 // The sort's kernels (keys, scatter, unsort) give each XCD contiguous ranges of particles, so that the runs they
@@ -359,7 +438,9 @@ __global__ __launch_bounds__(kNT) void k_scan_add(int* __restrict__ start, int c
 // measured slower (0.51 -> 0.54 ms).
 __global__ __launch_bounds__(kNT) void k_scatter(const SortJob* __restrict__ jobs, const int* __restrict__ offs,
                                                  int njob, int total, const int* __restrict__ key,
-                                                 const int* __restrict__ rank, const int* __restrict__ start) {
+                                                 const int* __restrict__ rank, const int* __restrict__ start,
+                                                 const DepJob* __restrict__ dep) {
+  if (dep) mark_split_tiles(to_const(dep)[0], start);
   for (int w = blockIdx.x; w < total; w += gridDim.x) {
     const int jb = __builtin_amdgcn_readfirstlane(find_job(to_const(offs), njob, w));
     const LPC_CONST SortJob& J = to_const(jobs)[jb];
@@ -400,12 +481,17 @@ __global__ __launch_bounds__(kNT) void k_scatter(const SortJob* __restrict__ job
 // integer weights of the corners that fall inside its tile with 64-bit LDS atomics; and writes every cell of the
 // tile once with plain stores (so the mesh needs no clearing and sees no global atomics). The up to 8 particle
 // ranges are walked as one index space, so a workgroup needs few rounds of loads.
-constexpr int kTileCells = kTX * kTY * kTZ;
+// A tile that holds many more particles than the others would keep one workgroup busy long after the rest: it is split
+// (mark_split_tiles), the chunks' workgroups add their counts in a slot with global atomics, and the last to arrive writes
+// the tile (70 % of the particles in eight clumps: 1.5 M on 270^3 0.63 -> 0.12 ms, 50 M on 480^3 11.8 -> 3.7 ms; each
+// chunk in a slot of its own, summed by the last, grew with the square of a tile's chunks: 22 ms).
+// 1024 threads per tile (for meshes of few, full tiles) measured slower: 16.7 M particles on 128^3 0.47 -> 0.60 ms.
 // A cell's exact count C is a sum of corner weights of at most 2^48 each. With fewer than 2^16 particles reaching a
 // tile, C < 2^64 cannot wrap its 64-bit sum and bit 63 tells whether C >= 2^63 (the headroom of a signed count).
 // A tile reached by 2^16 or more particles also sums the weights' high parts T = sum(w >> 16), which cannot wrap;
 // with the wrapped sum S = C mod 2^64, R = S - T 2^16 (mod 2^64) is the exact sum of the low parts (< 2^47), so
-// C = T 2^16 + R and C >= 2^63 exactly when T + (R >> 16) >= 2^47.
+// C = T 2^16 + R and C >= 2^63 exactly when T + (R >> 16) >= 2^47. (A split tile's chunks hold fewer than 2^16 particles
+// each; the tile sums their counts and, with 2^16 particles or more, the counts' high parts.)
 constexpr int kWrapParticles = 1 << 16;
 
 // The particle ranges of a tile's workgroup: logical particle q lies in range r when cum[r] <= q < cum[r + 1], at
@@ -415,20 +501,20 @@ struct TileRanges {
   int nr;
 };
 
-// Adds (corner weight >> shift) of every particle in the ranges to the tile's cells in acc (LDS).
-__device__ __forceinline__ void deposit_pass(const TileRanges tr, int tot, LPC_GLOBAL const float* __restrict__ pos,
+// Adds (corner weight >> shift) of the logical particles [beg, end) of the ranges to the tile's cells in acc (LDS).
+__device__ __forceinline__ void deposit_pass(const TileRanges tr, int beg, int end, LPC_GLOBAL const float* __restrict__ pos,
                                              int64_t n, double scale, int nm, int x0, int y0, int z0,
                                              unsigned long long* acc, int shift) {
   const int64_t period = static_cast<int64_t>(nm) << kFracBits;
   // kUnroll particles per thread per round: all their position loads are issued before any is used
   constexpr int kUnroll = 4;
-  for (int q0 = threadIdx.x; q0 < tot; q0 += kUnroll * kNT) {
+  for (int q0 = beg + static_cast<int>(threadIdx.x); q0 < end; q0 += kUnroll * kNT) {
     // every load is issued unconditionally (a thread past the end reloads the last particle and skips it below), so
     // the 3 kUnroll loads go out together instead of one conditional group at a time
     float px[kUnroll][3];
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) {
-      const int q = min(q0 + u * kNT, tot - 1);
+      const int q = min(q0 + u * kNT, end - 1);
       int off = tr.rb[0];
 #pragma unroll
       for (int r = 1; r < 8; ++r)
@@ -439,7 +525,7 @@ __device__ __forceinline__ void deposit_pass(const TileRanges tr, int tot, LPC_G
     }
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) {
-      if (q0 + u * kNT >= tot) continue;
+      if (q0 + u * kNT >= end) continue;
       uint32_t c[3], f[3];
       if (!fixed_coord3(px[u], scale, period, c, f)) continue;  // cannot happen for a bucketed particle
       // corner offsets relative to the tile origin (periodic), in [0, kT*) when inside
@@ -514,20 +600,12 @@ __device__ __forceinline__ bool write_tile_column(const unsigned long long* acc,
   return overflow;
 }
 
-__global__ __launch_bounds__(kNT) void k_deposit_tiles(const DepJob* __restrict__ jobs, const int* __restrict__ offs,
-                                                       int njob, int total, const int* __restrict__ start,
-                                                       int* __restrict__ flags) {
-  __shared__ __align__(16) unsigned long long acc[kTileCells];
-  const int w = blockIdx.x;
-  if (w >= total) return;
-  const int jb = __builtin_amdgcn_readfirstlane(find_job(to_const(offs), njob, w));
-  const LPC_CONST DepJob& J = to_const(jobs)[jb];
+// One tile (CHUNK false), or chunk `chunk` of a split tile.
+template <bool CHUNK>
+__device__ __forceinline__ void deposit_tile(const LPC_CONST DepJob& J, int t, int chunk,
+                                             const int* __restrict__ start, int* __restrict__ flags,
+                                             unsigned long long* acc) {
   const int ntx = J.ntx, nty = J.nty, ntz = J.ntz, nm = J.nm;
-  // neighbouring tiles (which share the particles of their boundary buckets) run on the same XCD
-  // tiles in XCD-contiguous chunks of 64 (at 768^3: 0.748 ms with eighths of the tiles per XCD, 0.736 ms with chunks
-  // of 32, 0.70 ms with 64; 48, 72, 96, 128 and 256 measured 0.71-0.75 ms)
-  const int t = xcd_chunk_remap(w - offs[jb], offs[jb + 1] - offs[jb], 64);
-  if (t >= ntx * nty * ntz) return;  // padding item
   const int tid = threadIdx.x;
   clear_tile(acc, tid);
   // t = (tx nty + ty) ntz + tz, split with the job's reciprocals instead of runtime divisions (exact: t < ntx nty ntz
@@ -539,31 +617,15 @@ __global__ __launch_bounds__(kNT) void k_deposit_tiles(const DepJob* __restrict_
   // the particle ranges (local indices, uniform): own tile, then the boundary bucket of each distinct lower
   // neighbour. All sixteen bucket bounds are loaded before any is used (one memory round trip, not eight).
   const int pbase = static_cast<int>(J.pbase);  // sort positions are int
-  // an axis with one tile has no distinct lower neighbour
-  const bool mx = ntx > 1, my = nty > 1, mz = ntz > 1;
-  int bs[8], es[8];
-#pragma unroll
-  for (int q = 0; q < 8; ++q) {
-    const int dx = (q >> 2) & 1, dy = (q >> 1) & 1, dz = q & 1;  // 1 = the lower neighbour along that axis
-    const bool use = (mx || !dx) && (my || !dy) && (mz || !dz);
-    const int sx = dx ? (tx == 0 ? ntx - 1 : tx - 1) : tx, sy = dy ? (ty == 0 ? nty - 1 : ty - 1) : ty,
-              sz = dz ? (tz == 0 ? ntz - 1 : tz - 1) : tz;
-    // always in range (an axis with one tile names the tile itself), so loaded without a branch; unused ones are
-    // skipped below
-    const int g = J.tbase + 2 * ((sx * nty + sy) * ntz + sz);
-    (void)use;
-    bs[q] = start[q == 0 ? g : g + 1];
-    es[q] = start[g + 2];
-  }
+  const TileBounds tb = tile_bounds(start, J.tbase, tx, ty, tz, ntx, nty, ntz);
   int rb[8], cum[9];
   int nr = 0;
   cum[0] = 0;
 #pragma unroll
   for (int q = 0; q < 8; ++q) {
-    const int dx = (q >> 2) & 1, dy = (q >> 1) & 1, dz = q & 1;
-    if ((mx || !dx) && (my || !dy) && (mz || !dz)) {
-      const int b = __builtin_amdgcn_readfirstlane(bs[q] - pbase);
-      const int e = __builtin_amdgcn_readfirstlane(es[q] - pbase);
+    if (tile_range_used(q, ntx, nty, ntz)) {
+      const int b = __builtin_amdgcn_readfirstlane(tb.b[q] - pbase);
+      const int e = __builtin_amdgcn_readfirstlane(tb.e[q] - pbase);
       rb[nr] = b;
       cum[nr + 1] = cum[nr] + (e - b);
       ++nr;
@@ -579,17 +641,51 @@ __global__ __launch_bounds__(kNT) void k_deposit_tiles(const DepJob* __restrict_
   }
   tr.cum[8] = tot;
   tr.nr = nr;
+  // a split tile: its chunks have their own workgroups
+  if (!CHUNK && tot > J.split.trigger && __builtin_amdgcn_readfirstlane(J.split.marker[t]) >= 0) return;
+  const int beg = CHUNK ? chunk * J.split.size : 0;
+  const int end = CHUNK ? min(tot, beg + J.split.size) : tot;
   __syncthreads();
   LPC_GLOBAL const float* pos = to_global(J.pos);
-  deposit_pass(tr, tot, pos, J.n, J.scale, nm, x0, y0, z0, acc, 0);
+  deposit_pass(tr, beg, end, pos, J.n, J.scale, nm, x0, y0, z0, acc, 0);
   __syncthreads();
+  bool overflow = false;
+  if constexpr (CHUNK) {
+    // add the chunk's counts to the tile's sums: the counts mod 2^64 and, where they could wrap, their high parts; the
+    // last workgroup of the tile to arrive takes the sums
+    const int slot = J.split.marker[t];
+    const int chunks = (tot + J.split.size - 1) / J.split.size;
+    const bool wraps = tot >= kWrapParticles;
+    unsigned long long* sum = J.split.sums + static_cast<size_t>(slot) * (2 * kTileCells);
+    for (int i = tid; i < kTileCells; i += kNT) {
+      const unsigned long long v = acc[i];
+      if (v) atomicAdd(sum + i, v);
+      if (v && wraps) atomicAdd(sum + kTileCells + i, v >> kFracBits);
+    }
+    __threadfence();
+    __syncthreads();
+    if (tid == 0) acc[0] = atomicAdd(J.split.arrive + slot, 1) == chunks - 1 ? 1 : 0;
+    __syncthreads();
+    const bool last = acc[0] != 0;
+    __syncthreads();
+    if (!last) return;  // (uniform)
+    __threadfence();
+    for (int i = tid; i < kTileCells; i += kNT) {
+      const unsigned long long S = __hip_atomic_load(sum + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (wraps) {
+        const unsigned long long T =
+            __hip_atomic_load(sum + kTileCells + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        overflow |= (T + ((S - (T << kFracBits)) >> kFracBits)) >= (1ull << 47);
+      }
+      acc[i] = S;
+    }
+  }
   // write the tile (cells outside the mesh on a narrow last tile are skipped): the exact int64 counts, and/or the
   // FP32 density contrast C mscale - 1 that the forward transform takes
   LPC_GLOBAL unsigned long long* C = to_global(reinterpret_cast<unsigned long long*>(J.dens));
   LPC_GLOBAL float* D = to_global(J.delta);
   const double mscale = J.mscale;
   const int wx_ = min(kTX, nm - x0), wy_ = min(kTY, nm - y0), wz_ = min(kTZ, nm - z0);
-  bool overflow = false;
   // kNT = kTY kTZ threads: thread (j, k) writes its cell of every x-plane i, stepping one plane (nm^2 cells) at a
   // time; a wave's store covers two whole 128-byte rows
   static_assert(kNT == kTY * kTZ, "one thread per (y, z) cell of a tile plane");
@@ -601,14 +697,14 @@ __global__ __launch_bounds__(kNT) void k_deposit_tiles(const DepJob* __restrict_
     if (D) overflow |= write_tile_column<true>(acc, tid, wx_, cell, plane, C, D, mscale);
     if (C) overflow |= write_tile_column<false>(acc, tid, wx_, cell, plane, C, D, mscale);
   }
-  if (tot >= kWrapParticles) {  // uniform; rare (a tile reached by 65536 particles or more)
+  if (!CHUNK && tot >= kWrapParticles) {  // uniform; rare (an unsplit tile reached by 65536 particles or more)
     unsigned long long S[kTX];
 #pragma unroll
     for (int i = 0; i < kTX; ++i) S[i] = acc[i * kNT + tid];
     __syncthreads();
     clear_tile(acc, tid);
     __syncthreads();
-    deposit_pass(tr, tot, pos, J.n, J.scale, nm, x0, y0, z0, acc, kFracBits);
+    deposit_pass(tr, 0, tot, pos, J.n, J.scale, nm, x0, y0, z0, acc, kFracBits);
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < kTX; ++i) {
@@ -618,6 +714,38 @@ __global__ __launch_bounds__(kNT) void k_deposit_tiles(const DepJob* __restrict_
     }
   }
   if (overflow) atomicOr(flags + kFlagOverflow, 1);
+}
+
+__global__ __launch_bounds__(kNT) void k_deposit_tiles(const DepJob* __restrict__ jobs, const int* __restrict__ offs,
+                                                       int njob, int total, const int* __restrict__ start,
+                                                       int* __restrict__ flags) {
+  __shared__ __align__(16) unsigned long long acc[kTileCells];
+  const int w = blockIdx.x;
+  if (w >= total) return;
+  const int jb = __builtin_amdgcn_readfirstlane(find_job(to_const(offs), njob, w));
+  const LPC_CONST DepJob& J = to_const(jobs)[jb];
+  // neighbouring tiles (which share the particles of their boundary buckets) run on the same XCD
+  // tiles in XCD-contiguous chunks of 64 (at 768^3: 0.748 ms with eighths of the tiles per XCD, 0.736 ms with chunks
+  // of 32, 0.70 ms with 64; 48, 72, 96, 128 and 256 measured 0.71-0.75 ms)
+  const int t = xcd_chunk_remap(w - offs[jb], offs[jb + 1] - offs[jb], 64);
+  if (t >= J.ntx * J.nty * J.ntz) return;  // padding item
+  deposit_tile<false>(J, t, 0, start, flags, acc);
+}
+
+// The chunks of a box's split tiles, kSplitBlocks workgroups over their list. (A kernel of its own: in one with the whole
+// tiles its code cost those 5 % at 768^3.)
+constexpr int kSplitBlocks = 512;
+__global__ __launch_bounds__(kNT) void k_deposit_chunks(const DepJob* __restrict__ jobs, const int* __restrict__ start,
+                                                        int* __restrict__ flags) {
+  __shared__ __align__(16) unsigned long long acc[kTileCells];
+  const LPC_CONST DepJob& J = to_const(jobs)[0];
+  const int entries = min(J.split.count[1], J.split.entries);
+  for (int e = blockIdx.x; e < entries; e += kSplitBlocks) {
+    const int2 item = J.split.list[e];
+    const int t = __builtin_amdgcn_readfirstlane(item.x), chunk = __builtin_amdgcn_readfirstlane(item.y);
+    if (t >= 0) deposit_tile<true>(J, t, chunk, start, flags, acc);
+    __syncthreads();  // acc is reused
+  }
 }
 
 // Copy sorted positions and momenta back to the caller's order.
@@ -968,31 +1096,37 @@ hipError_t launch_tile_key(const SortJob* jobs, WorkTable wt, int* cnt, int* key
 
 int scan_blocks(int count) { return (count + kScanBlock - 1) / kScanBlock; }
 
-hipError_t launch_scan(int* cnt, int* start, int count, int* block_sums, hipStream_t s) {
+hipError_t launch_scan(int* cnt, int* start, int count, int* block_sums, int* zero, hipStream_t s) {
   const int nb = scan_blocks(count);
   if (nb == 0) return hipErrorInvalidValue;
   if (count <= kScanOne) {
-    k_scan_one<<<1, kScanNT, 0, s>>>(cnt, start, count);
+    k_scan_one<<<1, kScanNT, 0, s>>>(cnt, start, count, zero);
     return hipGetLastError();
   }
   k_scan_local<<<nb, kNT, 0, s>>>(cnt, start, count, block_sums);
-  k_scan_sums<<<1, kNT, 0, s>>>(block_sums, nb, start, count);
+  k_scan_sums<<<1, kNT, 0, s>>>(block_sums, nb, start, count, zero);
   k_scan_add<<<nb, kNT, 0, s>>>(start, count, block_sums);
   return hipGetLastError();
 }
 
 hipError_t launch_scatter(const SortJob* jobs, WorkTable wt, const int* key, const int* rank, const int* start,
-                          hipStream_t s) {
+                          const DepJob* dep, hipStream_t s) {
   if (wt.total <= 0) return hipSuccess;
-  k_scatter<<<grid_of(wt), kNT, 0, s>>>(jobs, wt.offs, wt.njob, wt.total, key, rank, start);
+  if (dep && wt.njob != 1) return hipErrorInvalidValue;
+  k_scatter<<<grid_of(wt), kNT, 0, s>>>(jobs, wt.offs, wt.njob, wt.total, key, rank, start, dep);
   return hipGetLastError();
 }
 
-hipError_t launch_deposit_tiles(const DepJob* jobs, WorkTable wt, const int* start, int* flags, hipStream_t s) {
+hipError_t launch_deposit_tiles(const DepJob* jobs, WorkTable wt, const int* start, bool split, int* flags,
+                                hipStream_t s) {
   if (wt.total <= 0) return hipSuccess;
+  if (split && wt.njob != 1) return hipErrorInvalidValue;
+  if (split) k_deposit_chunks<<<kSplitBlocks, kNT, 0, s>>>(jobs, start, flags);
   k_deposit_tiles<<<static_cast<unsigned>(wt.total), kNT, 0, s>>>(jobs, wt.offs, wt.njob, wt.total, start, flags);
   return hipGetLastError();
 }
+
+size_t dep_split_slot_bytes() { return 2 * kTileCells * sizeof(unsigned long long); }
 
 hipError_t launch_unsort(const UnsortJob* jobs, WorkTable wt, hipStream_t s) {
   if (wt.total <= 0) return hipSuccess;
