@@ -426,6 +426,15 @@ class JobPack {
     }
     return reinterpret_cast<const float*>(dev_ + it->second);
   }
+  // the same in FP64 (the statistics' window)
+  const double* sinc2_fp64(int n) {
+    std::vector<double> t(static_cast<size_t>(n / 2 + 1), 1.0);
+    for (int m = 1; m <= n / 2; ++m) {
+      const double x = M_PI * static_cast<double>(m) / n, v = std::sin(x) / x;
+      t[static_cast<size_t>(m)] = v * v;
+    }
+    return static_cast<const double*>(data(t.data(), t.size() * sizeof(double)));
+  }
   // Device copy of n bytes of host data (uploaded with the tables).
   const void* data(const void* p, size_t n) { return dev_ + append(p, n); }
   template <class J>
@@ -1882,6 +1891,7 @@ lpc_status lpc_power_spectrum(const lpc_geometry* geom, const float* pos, int64_
     unsigned long long* counts = reinterpret_cast<unsigned long long*>(sums + 2 * n_bins);
     JobPack jp(at(ws, p.jobs));
     const DensitySpectrum ds = add_density_spectrum(jp, ws, p, geom, pos, n, LPC_OP_POWER_SPECTRUM, A);
+    const double* window = jp.sinc2_fp64(nm);
     jp.upload(s);
     stage("clear", s, [&] { return kern::clear_call(flags, ds.ss.cnt, ds.ss.G, s); });
     stage("clear bins", s, [&] {
@@ -1890,7 +1900,7 @@ lpc_status lpc_power_spectrum(const lpc_geometry* geom, const float* pos, int64_
     run_density_spectrum(jp, ds, flags, s);
     const double V = geom->box * geom->box * geom->box;
     const double pscale = V / (static_cast<double>(M) * static_cast<double>(M));
-    stage("pk bin", s, [&] { return kern::pk_bin(A, nm, pitch, geom->box, k_max, n_bins, pscale, sums, counts, s); });
+    stage("pk bin", s, [&] { return kern::pk_bin(A, window, nm, pitch, geom->box, k_max, n_bins, pscale, sums, counts, s); });
     std::vector<double> hs(static_cast<size_t>(3) * n_bins);
     check(hipMemcpyAsync(hs.data(), sums, hs.size() * sizeof(double), hipMemcpyDeviceToHost, s), "copy bins");
     lpc_status st = finish(flags, s);
@@ -2012,12 +2022,7 @@ lpc_status lpc_bispectrum(const lpc_geometry* geom, const float* pos, int64_t n,
     sp.tw = jp.twiddles(sp.pl);
     sp.twh = jp.twiddles(sp.plh);
     sp.roots = jp.half_roots(nm);
-    std::vector<double> win(static_cast<size_t>(nm / 2 + 1), 1.0);
-    for (int i = 1; i <= nm / 2; ++i) {
-      const double x = M_PI * static_cast<double>(i) / nm, v = std::sin(x) / x;
-      win[static_cast<size_t>(i)] = v * v;
-    }
-    sp.win = static_cast<const double*>(jp.data(win.data(), win.size() * sizeof(double)));
+    sp.win = jp.sinc2_fp64(nm);
     const auto* shells_dev = static_cast<const kern::ShellPower*>(jp.data(shells.data(), shells.size() * sizeof(shells[0])));
     for (Group& g : groups) {
       g.fields_dev = static_cast<const kern::ShellField*>(jp.data(g.fields.data(), g.fields.size() * sizeof(g.fields[0])));

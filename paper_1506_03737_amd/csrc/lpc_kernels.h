@@ -438,9 +438,10 @@ hipError_t shell_power(const ShellPasses& a, const ShellPower* shells, int nshel
 // out[r] = the sum of parts[r][0 .. sum_blocks()) in a fixed order
 hipError_t sum_parts(const double* parts, int rows, double* out, hipStream_t s);
 int sum_blocks();
-// Power-spectrum binning of a half spectrum: sums[b] += (k, P) per mode, counts[b] += multiplicity.
-hipError_t pk_bin(const float2* spec, int nm, int pitch, double box, double k_max, int n_bins, double pscale,
-                  double* sums, unsigned long long* counts, hipStream_t s);
+// Power-spectrum binning of a half spectrum: sums[b] += (k, P) per mode, counts[b] += multiplicity. window: sinc^2(pi m /
+// nm), m <= nm / 2.
+hipError_t pk_bin(const float2* spec, const double* window, int nm, int pitch, double box, double k_max, int n_bins,
+                  double pscale, double* sums, unsigned long long* counts, hipStream_t s);
 
 }  // namespace kern
 }  // namespace lpc
