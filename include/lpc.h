@@ -322,8 +322,8 @@ typedef struct {
   int32_t c2r_rows;
 } lpc_fft_tiling;
 
-/* The built-in tiling of mesh size n (the widest widths that fit, with the fused pass at most 16 and 8 above
- * n = 512): host only. LPC_ERR_UNSUPPORTED_SIZE for a mesh size the FFTs do not take. */
+/* The built-in tiling of mesh size n (from measurements over 48 <= n <= 1024; what each stage's line is stands at the rule
+ * in abi.hip): host only. LPC_ERR_UNSUPPORTED_SIZE for a mesh size the FFTs do not take. */
 lpc_status lpc_fft_tiling_default(int32_t n_mesh, lpc_fft_tiling* out);
 /* The tiling in effect for mesh size n: the override set by lpc_fft_tiling_set, else the built-in one. */
 lpc_status lpc_fft_tiling_get(int32_t n_mesh, lpc_fft_tiling* out);

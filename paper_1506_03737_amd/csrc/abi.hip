@@ -273,13 +273,22 @@ lpc_status check_mesh(int nm, const char* what) {
   return LPC_OK;
 }
 
+Plan1D plan_of(int n, bool radix12 = true);
+
 // FFT tile widths per mesh size: the built-in rule, and overrides set through lpc_fft_tiling_set.
 lpc_fft_tiling default_tiling(int n) {
   lpc_fft_tiling t;
   t.z_rows = std::max(8, kern::z_rows(n, 1));
-  t.axis_cols = kern::strided_cols(n);
-  t.poisson_cols = std::min(16, kern::strided_cols(n));
-  t.c2r_rows = std::max(4, std::min(16, kern::z_rows(n, 3)));
+  // 16 columns rather than 32 above n = 200 (inverse y at 240^3 77 -> 68 us, at 256^3 68 -> 62; equal at 200^3)
+  t.axis_cols = n <= 200 ? 32 : kern::strided_cols(n, 16);
+  // The fused x pass keeps psi_hat in registers up to 12 points per thread; above that it holds a second tile in LDS and
+  // has one workgroup per CU: 16 columns to n = 384, 8 to 768, 4 above (400^3 587 us with 16 and 376 with 8, 512^3 907
+  // and 593; 864^3 6.5 ms with 8 and 4.3 with 4, 960^3 8.0 and 5.5; at 360^3 256 with 16 and 284 with 8). The chained
+  // form takes 8 columns at any size (256^3 60 -> 50, 320^3 112 -> 90; a batch of 192, 256 and 320 3.36 -> 3.18 ms).
+  t.poisson_cols = kern::poisson_chainable(plan_of(n)) ? 8 : (n <= 384 ? 16 : (n <= 768 ? 8 : 4));
+  // Fewer rows than fit put more workgroups on a CU: 16 to n = 240, 8 to 480, 4 above (240^3 86 us with either, 256^3 99
+  // with 16 and 88 with 8, 300^3 176 and 151; 480^3 566 with 8 and 640 with 4, 512^3 736 and 684, 600^3 1227 and 1101).
+  t.c2r_rows = n <= 240 ? 16 : (n <= 480 ? 8 : 4);
   return t;
 }
 
@@ -458,7 +467,7 @@ class JobPack {
   std::map<int, size_t> roots_, win_;
 };
 
-Plan1D plan_of(int n, bool radix12 = true) {
+Plan1D plan_of(int n, bool radix12) {
   Plan1D p;
   if (!kern::make_plan(n, &p, radix12)) throw HipError{hipErrorInvalidValue, "unsupported FFT length"};
   return p;
@@ -479,11 +488,13 @@ struct R2CSections {
   Section z, y, x;
   int Bz, Pz, Bax, Pax;
   size_t lds_z, lds_ax;
+  bool fixed;  // the strided passes' plan is compiled in
 };
 struct C2RSections {
   Section x, y, z;
   int Bax, R, Pax;
   size_t lds_ax, lds_z;
+  bool fixed;
 };
 
 kern::AxisJob axis_job(JobPack& jp, float2* base, int n, int64_t astr, int64_t ostr, int64_t cstr, int B) {
@@ -512,6 +523,7 @@ R2CSections add_r2c(JobPack& jp, const void* in, bool fixed, double mscale, int 
   r.Pz = kern::r2c_points(n, r.Bz);
   r.lds_z = kern::lds_z_r2c(n, r.Bz);
   r.lds_ax = kern::lds_axis(n, r.Bax);
+  r.fixed = kern::has_fixed_plan(plan_of(n));
   kern::ZR2CJob z{};
   z.in = in;
   z.out = out;
@@ -539,6 +551,7 @@ C2RSections add_c2r(JobPack& jp, float2* spec, int n, float* out, float scale) {
   c.R = t.z_rows;
   c.Pax = kern::axis_points(n, c.Bax);
   c.lds_ax = kern::lds_axis(n, c.Bax);
+  c.fixed = kern::has_fixed_plan(plan_of(n));
   c.lds_z = kern::lds_z_c2r(n, c.R);
   kern::AxisJob x = axis_job(jp, spec, n, static_cast<int64_t>(n) * pitch, pitch, 0, c.Bax);
   c.x = jp.add1(x, x.per_comp);
@@ -562,13 +575,13 @@ void run_r2c(const JobPack& jp, const R2CSections& r, bool fixed, int* flags, hi
   stage("fft z r2c", s, [&] {
     return kern::launch_z_r2c(jp.jobs<kern::ZR2CJob>(r.z), jp.table(r.z), fixed, r.Bz, r.Pz, r.lds_z, flags, s);
   });
-  stage("fft y", s, [&] { return kern::launch_axis(jp.jobs<kern::AxisJob>(r.y), jp.table(r.y), false, r.Bax, r.Pax, r.lds_ax, s); });
-  stage("fft x", s, [&] { return kern::launch_axis(jp.jobs<kern::AxisJob>(r.x), jp.table(r.x), false, r.Bax, r.Pax, r.lds_ax, s); });
+  stage("fft y", s, [&] { return kern::launch_axis(jp.jobs<kern::AxisJob>(r.y), jp.table(r.y), false, r.Bax, r.Pax, r.fixed, r.lds_ax, s); });
+  stage("fft x", s, [&] { return kern::launch_axis(jp.jobs<kern::AxisJob>(r.x), jp.table(r.x), false, r.Bax, r.Pax, r.fixed, r.lds_ax, s); });
 }
 
 void run_c2r(const JobPack& jp, const C2RSections& c, hipStream_t s) {
-  stage("fft x inv", s, [&] { return kern::launch_axis(jp.jobs<kern::AxisJob>(c.x), jp.table(c.x), true, c.Bax, c.Pax, c.lds_ax, s); });
-  stage("fft y inv", s, [&] { return kern::launch_axis(jp.jobs<kern::AxisJob>(c.y), jp.table(c.y), true, c.Bax, c.Pax, c.lds_ax, s); });
+  stage("fft x inv", s, [&] { return kern::launch_axis(jp.jobs<kern::AxisJob>(c.x), jp.table(c.x), true, c.Bax, c.Pax, c.fixed, c.lds_ax, s); });
+  stage("fft y inv", s, [&] { return kern::launch_axis(jp.jobs<kern::AxisJob>(c.y), jp.table(c.y), true, c.Bax, c.Pax, c.fixed, c.lds_ax, s); });
   stage("fft z c2r", s, [&] { return kern::launch_z_c2r(jp.jobs<kern::ZC2RJob>(c.z), jp.table(c.z), 1, c.R, 0, c.lds_z, s); });
 }
 
@@ -592,16 +605,22 @@ struct ForceBox {
 struct ForceProgram {
   // sorting: user -> copy 0; copy c -> copy 1 - c; per-copy particle stages
   Section sort_user, sort_next[2], dep[2], parts[2], frame[2], unsort[2];
-  Section zr2c, yfwd, pois, yinv, zc2r;
-  int Bz = 32, Bax = 32, Bp = 16, R3 = 16;
-  int Mp = 8;  // points per thread of the fused x + Poisson tiles: the largest over the boxes
-  bool chain_p = false;  // the fused x pass chains its transforms through registers (every plan 8 x 8 x R, 8 columns)
+  Section zr2c, yfwd, yinv, zc2r;
+  int Bz = 32, Bax = 32, R3 = 16;
+  // The fused x pass of the boxes whose transforms chain through registers (plan 8 x 8 x R or 4 x 4 x 8 x 8 and 8 columns)
+  // and of the others: two launches, so that a box takes the form that it takes by itself.
+  struct Pois {
+    Section sec;
+    int B = 16, M = 8;  // the narrowest width and the most points per thread over the boxes
+    size_t lds = 0;
+  } pois[2];  // [1]: chained
   int P3 = 8;  // points per thread of the three-spectrum c2r tiles: the largest over the boxes
   int Pax = 8;  // points per thread of the strided y tiles: the largest over the boxes
   int Pz = 8;   // points per thread of the forward z tiles: the largest over the boxes
-  size_t lds_z = 0, lds_ax = 0, lds_p = 0, lds_c = 0;
+  size_t lds_z = 0, lds_ax = 0, lds_c = 0;
   SortSpace ss;
   bool cola_run = false;
+  bool fixed = true;      // every box's strided passes have compiled plans
   bool fixed_in = false;  // the deposit writes int64 counts for the forward transform (else the FP32 contrast)
   int* split_count = nullptr;  // a single box whose heavy tiles the deposit may split
 };
@@ -649,22 +668,26 @@ ForceProgram add_force(JobPack& jp, const std::vector<ForceBox>& boxes, const So
   f.ss = ss;
   f.cola_run = cola_run;
   for (const ForceBox& b : boxes) f.fixed_in |= b.keep_counts;
+  std::vector<int> chained;  // per box (another thread may set a tiling meanwhile: it is read once)
   for (const ForceBox& b : boxes) {
     // widths fit every smaller size too, so the smallest over the boxes fits all of them
     const lpc_fft_tiling t = tiling_of(b.nm);
     f.Bz = std::min(f.Bz, t.z_rows);
     f.Bax = std::min(f.Bax, t.axis_cols);
-    f.Bp = std::min(f.Bp, t.poisson_cols);
+    chained.push_back(t.poisson_cols == 8 && kern::poisson_chainable(plan_of(b.nm)));
+    int& Bp = f.pois[chained.back()].B;
+    Bp = std::min(Bp, t.poisson_cols);
     f.R3 = std::min(f.R3, t.c2r_rows);
   }
-  for (const ForceBox& b : boxes) {
-    f.Mp = std::max(f.Mp, kern::poisson_points(b.nm, f.Bp));
+  for (size_t ib = 0; ib < boxes.size(); ++ib) {
+    const ForceBox& b = boxes[ib];
+    ForceProgram::Pois& fp = f.pois[chained[ib]];
+    fp.M = std::max(fp.M, kern::poisson_points(b.nm, fp.B));
     f.P3 = std::max(f.P3, kern::c2r_points(b.nm, f.R3));
     f.Pax = std::max(f.Pax, kern::axis_points(b.nm, f.Bax));
     f.Pz = std::max(f.Pz, kern::r2c_points(b.nm, f.Bz));
+    f.fixed = f.fixed && kern::has_fixed_plan(y_plan_of(b.nm));
   }
-  f.chain_p = f.Bp == 8;
-  for (const ForceBox& b : boxes) f.chain_p = f.chain_p && kern::poisson_chainable(plan_of(b.nm));
   const int ncopy = cola_run ? 2 : 1;
   std::vector<kern::SortJob> su, sn[2];
   std::vector<kern::DepJob> dj[2];
@@ -673,9 +696,9 @@ ForceProgram add_force(JobPack& jp, const std::vector<ForceBox>& boxes, const So
   std::vector<kern::ZR2CJob> zs;
   std::vector<kern::AxisJob> ys;
   std::vector<kern::YGradJob> yis;
-  std::vector<kern::PoissonJob> ps;
+  std::vector<kern::PoissonJob> ps[2];
   std::vector<kern::ZC2RJob> cs;
-  std::vector<int> i_part, i_frame, i_tile, i_z, i_y, i_yi, i_p, i_c;
+  std::vector<int> i_part, i_frame, i_tile, i_z, i_y, i_yi, i_p[2], i_c;
   for (size_t ib = 0; ib < boxes.size(); ++ib) {
     const ForceBox& b = boxes[ib];
     const int nm = b.nm, pitch = kern::mesh_pitch(nm), nh = nm / 2 + 1;
@@ -807,7 +830,9 @@ ForceProgram add_force(JobPack& jp, const std::vector<ForceBox>& boxes, const So
     p.C = b.C;
     p.nm = nm;
     p.pitch = pitch;
-    p.ntc = (nh + f.Bp - 1) / f.Bp;
+    const int ch = chained[ib];
+    ForceProgram::Pois& fp = f.pois[ch];
+    p.ntc = (nh + fp.B - 1) / fp.B;
     p.deconv = deconv;
     p.kf = static_cast<float>(2.0 * M_PI / b.box);
     p.inv_m3 = static_cast<float>(1.0 / static_cast<double>(M));
@@ -815,8 +840,8 @@ ForceProgram add_force(JobPack& jp, const std::vector<ForceBox>& boxes, const So
     p.tw = jp.twiddles(p.pl);
     p.tw_rev = jp.twiddles(kern::reversed_plan(p.pl));
     p.win = jp.sinc2(nm);
-    ps.push_back(p);
-    i_p.push_back(nm * p.ntc);
+    ps[ch].push_back(p);
+    i_p[ch].push_back(nm * p.ntc);
     kern::ZC2RJob c{};
     c.in0 = b.A;
     c.in1 = b.B;
@@ -835,7 +860,7 @@ ForceProgram add_force(JobPack& jp, const std::vector<ForceBox>& boxes, const So
     i_c.push_back((c.nrows + f.R3 - 1) / f.R3);
     f.lds_z = std::max(f.lds_z, kern::lds_z_r2c(nm, f.Bz));
     f.lds_ax = std::max(f.lds_ax, kern::lds_axis(nm, f.Bax));
-    f.lds_p = std::max(f.lds_p, kern::lds_x_poisson(nm, f.Bp, f.Mp, f.chain_p));
+    fp.lds = std::max(fp.lds, kern::lds_x_poisson(nm, fp.B, fp.M, ch != 0));
     f.lds_c = std::max(f.lds_c, kern::lds_z_c2r(nm, 3 * f.R3));
   }
   f.sort_user = jp.add(su, i_part);
@@ -848,7 +873,8 @@ ForceProgram add_force(JobPack& jp, const std::vector<ForceBox>& boxes, const So
   }
   f.zr2c = jp.add(zs, i_z);
   f.yfwd = jp.add(ys, i_y);
-  f.pois = jp.add(ps, i_p);
+  for (int ch = 0; ch < 2; ++ch)
+    if (!ps[ch].empty()) f.pois[ch].sec = jp.add(ps[ch], i_p[ch]);
   f.yinv = jp.add(yis, i_yi);
   f.zc2r = jp.add(cs, i_c);
   return f;
@@ -882,9 +908,13 @@ void run_force_mesh(const JobPack& jp, const ForceProgram& f, int c, int* flags,
     return kern::launch_z_r2c(jp.jobs<kern::ZR2CJob>(f.zr2c), jp.table(f.zr2c), f.fixed_in, f.Bz, f.Pz, f.lds_z, flags,
                               s);
   });
-  stage("fft y", s, [&] { return kern::launch_axis(jp.jobs<kern::AxisJob>(f.yfwd), jp.table(f.yfwd), false, f.Bax, f.Pax, f.lds_ax, s); });
-  stage("fft x + poisson", s, [&] { return kern::launch_poisson(jp.jobs<kern::PoissonJob>(f.pois), jp.table(f.pois), f.Bp, f.Mp, f.chain_p, f.lds_p, s); });
-  stage("fft y inv", s, [&] { return kern::launch_y_grad(jp.jobs<kern::YGradJob>(f.yinv), jp.table(f.yinv), f.Bax, f.Pax, f.lds_ax, s); });
+  stage("fft y", s, [&] { return kern::launch_axis(jp.jobs<kern::AxisJob>(f.yfwd), jp.table(f.yfwd), false, f.Bax, f.Pax, f.fixed, f.lds_ax, s); });
+  for (int ch = 0; ch < 2; ++ch) {
+    const ForceProgram::Pois& fp = f.pois[ch];
+    if (fp.lds == 0) continue;  // no box takes this form
+    stage("fft x + poisson", s, [&] { return kern::launch_poisson(jp.jobs<kern::PoissonJob>(fp.sec), jp.table(fp.sec), fp.B, fp.M, ch != 0, fp.lds, s); });
+  }
+  stage("fft y inv", s, [&] { return kern::launch_y_grad(jp.jobs<kern::YGradJob>(f.yinv), jp.table(f.yinv), f.Bax, f.Pax, f.fixed, f.lds_ax, s); });
   stage("fft z c2r", s, [&] { return kern::launch_z_c2r(jp.jobs<kern::ZC2RJob>(f.zc2r), jp.table(f.zc2r), 3, f.R3, f.P3, f.lds_c, s); });
 }
 
@@ -1588,6 +1618,7 @@ lpc_status init_ic_impl(const lpc_geometry* geom, const lpc_cosmology* cosmo, ui
     const float2 *tw = jp.twiddles(full), *twh = jp.twiddles(hplan), *roots = jp.half_roots(N);
     const int Bax = tiling_of(N).axis_cols, Pax = kern::axis_points(N, Bax);
     const size_t lds_ax = kern::lds_axis(N, Bax);
+    const bool fixed = kern::has_fixed_plan(full);
     // forward y pass of meshes m[0..count), without the kz = N / 2 column
     auto y_forward = [&](float2* const* m, int count) {
       std::vector<kern::AxisJob> jobs;
@@ -1604,7 +1635,7 @@ lpc_status init_ic_impl(const lpc_geometry* geom, const lpc_cosmology* cosmo, ui
     };
     auto run_y = [&](const Section& sec, bool inverse) {
       stage(inverse ? "ic y inv" : "ic y", s, [&] {
-        return kern::launch_axis(jp.jobs<kern::AxisJob>(sec), jp.table(sec), inverse, Bax, Pax, lds_ax, s);
+        return kern::launch_axis(jp.jobs<kern::AxisJob>(sec), jp.table(sec), inverse, Bax, Pax, fixed, lds_ax, s);
       });
     };
     const Section y_noise = y_forward(&A, 1);
@@ -1781,7 +1812,7 @@ lpc_status init_ic_impl(const lpc_geometry* geom, const lpc_cosmology* cosmo, ui
     x2.out[1] = C;
     x2.kind[1] = 0;
     stage("ic x", s, [&] { return kern::ic_x(x2, s); });
-    stage("ic y inv", s, [&] { return kern::launch_y_grad(jp.jobs<kern::YGradJob>(y_psi2), jp.table(y_psi2), Bax, Pax, lds_ax, s); });
+    stage("ic y inv", s, [&] { return kern::launch_y_grad(jp.jobs<kern::YGradJob>(y_psi2), jp.table(y_psi2), Bax, Pax, fixed, lds_ax, s); });
     const double d1 = host::growth_D1(c, a_init), d2 = host::growth_D2(c, a_init);
     const double E = host::hubble_E(c, a_init), a3 = a_init * a_init * a_init;
     kern::IcZ z2 = zi;

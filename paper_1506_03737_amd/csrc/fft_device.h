@@ -473,14 +473,107 @@ struct FixedFFT {
   }
 };
 
-// All stages of plan `pl` over the B columns of the tile (row pitch BP). tw is the plan's per-stage twiddle
-// table. The caller has synchronised after filling the tile. With R12 false the radix-12 stage is not compiled in
-// (for a kernel at its register cap): the plan must then come from make_plan(n, p, false).
-template <bool INV, int EPT = kEPT, bool R12 = true, class PL>
-__device__ __forceinline__ void fft_tile(float2* tile, const float2* tw, const PL& pl, int B, int BP, int tid) {
+// The first and the last stage of a run-time plan fed from and drained to global memory, as FirstStage and
+// fft_stage_to_global do for compile-time ones (the tile is neither filled first nor read back at the end).
+template <int R, bool INV, int EPT, class Load, class Mid>
+__device__ __forceinline__ void fft_stage_load(float2* tile, int n, const TileGeom& g, Load load, Mid mid) {
+  constexpr int MB = (EPT + R - 1) / R;
+  const int T = n / R;
+  float2 v[MB][R];
+#pragma unroll
+  for (int m = 0; m < MB; ++m) {
+    const int i = g.i0 + m * g.S;
+    if (i < T) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) v[m][r] = load(i + r * T, g.b);
+    }
+  }
+  mid();
+#pragma unroll
+  for (int m = 0; m < MB; ++m) {
+    const int i = g.i0 + m * g.S;
+    if (i < T) {
+      Dft<R, INV>::run(v[m]);
+      float2* dst = tile + i * R * g.BP + g.b;
+#pragma unroll
+      for (int r = 0; r < R; ++r) dst[r * g.BP] = v[m][r];
+    }
+  }
+  __syncthreads();
+}
+// (pairs of columns from one source column: see FirstStagePairs)
+template <int R, bool INV, int EPT, class Load, class Pair, class Mid>
+__device__ __forceinline__ void fft_stage_load_pairs(float2* tile, int n, int B, int BP, int tid, Load load, Pair pair,
+                                                     Mid mid) {
+  constexpr int MB = (EPT + 2 * R - 1) / (2 * R);
+  const int T = n / R, BH = B / 2, S = kFftNT / BH, bh = tid % BH, i0 = tid / BH;
+  float2 x[MB][R];
+#pragma unroll
+  for (int m = 0; m < MB; ++m) {
+    const int i = i0 + m * S;
+    if (i < T) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) x[m][r] = load(i + r * T, bh);
+    }
+  }
+  mid();
+#pragma unroll
+  for (int m = 0; m < MB; ++m) {
+    const int i = i0 + m * S;
+    if (i < T) {
+      float2 a[R];
+#pragma unroll
+      for (int r = 0; r < R; ++r) a[r] = pair(i + r * T, x[m][r]);
+      Dft<R, INV>::run(a);
+      Dft<R, INV>::run(x[m]);
+      float2* dst = tile + i * R * BP + bh;
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        dst[r * BP] = a[r];
+        dst[r * BP + BH] = x[m][r];
+      }
+    }
+  }
+  __syncthreads();
+}
+template <int R, bool INV, int EPT, class Store>
+__device__ __forceinline__ void fft_stage_store(const float2* tile, const float2* tws, int n, int p, int pmask,
+                                                const TileGeom& g, Store store) {
+  constexpr int MB = (EPT + R - 1) / R;
+  const int T = n / R;
+  float2 v[MB][R];
+#pragma unroll
+  for (int m = 0; m < MB; ++m) {
+    const int i = g.i0 + m * g.S;
+    if (i < T) {
+      const float2* src = tile + i * g.BP + g.b;
+#pragma unroll
+      for (int r = 0; r < R; ++r) v[m][r] = src[r * T * g.BP];
+    }
+  }
+#pragma unroll
+  for (int m = 0; m < MB; ++m) {
+    const int i = g.i0 + m * g.S;
+    if (i < T) {
+      const int k = (pmask >= 0) ? (i & pmask) : (i % p);
+      const float2* w = tws + k * (R - 1) - 1;
+#pragma unroll
+      for (int r = 1; r < R; ++r) v[m][r] = INV ? cmulc(v[m][r], w[r]) : cmul(v[m][r], w[r]);
+      Dft<R, INV>::run(v[m]);
+      const int row = (i - k) * R + k;
+#pragma unroll
+      for (int r = 0; r < R; ++r) store(row + r * p, g.b, v[m][r]);
+    }
+  }
+}
+
+// Stages s0 .. s1 - 1 of plan `pl` over the B columns of the tile.
+template <bool INV, int EPT, bool R12, class PL>
+__device__ __forceinline__ void fft_tile_stages(float2* tile, const float2* tw, const PL& pl, int B, int BP, int tid, int s0,
+                                                int s1) {
   const TileGeom g(B, BP, tid);
   const int n = pl.n;
-  for (int s = 0; s < pl.nst; ++s) {
+  for (int s = s0; s < s1; ++s) {
     const float2* tws = tw + pl.tw_off[s];
     const int p = pl.p[s], pm = pl.pmask[s];
     switch (pl.radix[s]) {  // the plans use radices 8, 4, 2, 12, 3 and 5 (make_plan)
@@ -494,6 +587,14 @@ __device__ __forceinline__ void fft_tile(float2* tile, const float2* tw, const P
       default: fft_stage<5, INV, EPT>(tile, tws, n, p, pm, g); break;
     }
   }
+}
+
+// All stages of plan `pl` over the B columns of the tile (row pitch BP). tw is the plan's per-stage twiddle
+// table. The caller has synchronised after filling the tile. With R12 false the radix-12 stage is not compiled in
+// (for a kernel at its register cap): the plan must then come from make_plan(n, p, false).
+template <bool INV, int EPT = kEPT, bool R12 = true, class PL>
+__device__ __forceinline__ void fft_tile(float2* tile, const float2* tw, const PL& pl, int B, int BP, int tid) {
+  fft_tile_stages<INV, EPT, R12>(tile, tw, pl, B, BP, tid, 0, pl.nst);
 }
 
 

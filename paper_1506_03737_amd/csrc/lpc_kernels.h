@@ -273,7 +273,7 @@ struct ZC2RJob {        // inverse z pass of NC spectra of one mesh
 };
 
 // Tile geometry chosen for one transform length (shared by the host builder and the launchers).
-int strided_cols(int n);          // B of strided passes
+int strided_cols(int n, int most = 32);          // B of strided passes
 int z_rows(int n, int nc);        // rows per z-pass tile for nc interleaved spectra
 // Tile widths the FFT kernels are instantiated for, and whether width w fits length n (stage and load capacity of a
 // tile, 160 KiB of LDS).
@@ -315,8 +315,14 @@ hipError_t launch_frame(const PartJob* jobs, WorkTable wt, float f1, float f2, h
 void init_kernels();
 hipError_t launch_z_r2c(const ZR2CJob* jobs, WorkTable wt, bool fixed, int B, int P, size_t lds, int* flags,
                         hipStream_t s);
-hipError_t launch_axis(const AxisJob* jobs, WorkTable wt, bool inverse, int B, int P, size_t lds, hipStream_t s);
-hipError_t launch_y_grad(const YGradJob* jobs, WorkTable wt, int B, int P, size_t lds, hipStream_t s);
+void init_axis();
+void init_y_grad();
+void init_poisson();
+// fixed_plans: every job's plan is one that the strided passes carry compiled (has_fixed_plan)
+bool has_fixed_plan(const Plan1D& pl);
+hipError_t launch_axis(const AxisJob* jobs, WorkTable wt, bool inverse, int B, int P, bool fixed_plans, size_t lds,
+                       hipStream_t s);
+hipError_t launch_y_grad(const YGradJob* jobs, WorkTable wt, int B, int P, bool fixed_plans, size_t lds, hipStream_t s);
 // chained: every job's plan is poisson_chainable and B = 8 (the transforms chained through registers)
 hipError_t launch_poisson(const PoissonJob* jobs, WorkTable wt, int B, int M, bool chained, size_t lds, hipStream_t s);
 // Plans 8 x 8 x R with R in {12, 5, 4, 3}, and 4 x 4 x 8 x 8: the fused x pass can chain its transforms through
