@@ -1,7 +1,6 @@
 // Kernels of the learned displacement correction (declared in net_kernels.h). The 3^3 convolutions (forward, data
-// gradient, and weight gradient on grids a multiple of 32 per side) and the forward 2^3 down/up layers run on BF16
-// MFMA with FP32 accumulation; the 2^3 data gradients, the other weight gradients and the element-wise steps run on
-// the vector ALUs. Weight gradients are FP32 partial sums per voxel chunk, reduced in a fixed order.
+// gradient and weight gradient) and the 2^3 down/up layers run on BF16 MFMA with FP32 accumulation; the element-wise steps
+// run on the vector ALUs. Weight gradients are FP32 partial sums per voxel chunk, reduced in a fixed order.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -378,101 +377,9 @@ __global__ __launch_bounds__(kNT) void k_transpose2(const float* __restrict__ W,
 }
 
 // ---------------------------------------------------------------------------------------------------------------
-// Weight gradient of a 3^3 layer on the vector ALUs, for grids that are not a multiple of 32 per side (the MFMA
-// kernels below take the rest). Workgroup (chunk, tap) sums dz[p][o] x[p + d_tap][i] over the output voxels p of its
-// chunk, for every (o, i); tap 0 also sums dz[p][o] for the bias. Voxels, tiles of kTV, are staged in LDS as FP32;
-// thread groups take interleaved voxels of a tile and are reduced in LDS at the end.
-constexpr int kTV = 64;
-constexpr int kMaxC = 64;
+constexpr int kMaxC = 64;  // channels of the widest layer
 
-__device__ __forceinline__ int conv3_neighbour(int p, int tap, int D) {  // periodic voxel p + d_tap
-  const int px = p / (D * D), py = (p / D) % D, pz = p % D;
-  const int x = wrapi(px + tap / 9 - 1, D), y = wrapi(py + (tap / 3) % 3 - 1, D), z = wrapi(pz + tap % 3 - 1, D);
-  return (x * D + y) * D + z;
-}
-
-template <int CI>
-__global__ __launch_bounds__(kNT) void k_wgrad(View x, int cin, int cin_real, View dz, int cout, int D,
-                                               float* __restrict__ partial) {
-  constexpr int ntap = 27;
-  const int nbase = D * D * D;
-  __shared__ float sdz[kTV * kMaxC];
-  __shared__ float sx[kTV * kMaxC];
-  __shared__ int sxv[kTV], szv[kTV];
-  const int chunk = blockIdx.x, tap = blockIdx.y, nchunk = gridDim.x;
-  const int tid = threadIdx.x;
-  const int ncb = cin / CI;
-  const int npb = cout * ncb;           // (o, ci-block) pairs
-  const int G = kNT / npb;              // thread groups over voxels
-  const int pb = tid % npb, grp = tid / npb;
-  const bool active = grp < G;
-  const int o = pb / ncb, cb = pb % ncb;
-  float acc[CI];
-#pragma unroll
-  for (int c = 0; c < CI; ++c) acc[c] = 0.f;
-  float accb = 0.f;
-  const int64_t per = (static_cast<int64_t>(nbase) + nchunk - 1) / nchunk;
-  const int b0 = static_cast<int>(per * chunk);
-  const int b1 = static_cast<int>(std::min<int64_t>(nbase, per * (chunk + 1)));
-  const int gz = (cout + 7) / 8, gx = cin / 8;  // 16-byte groups per voxel (dz views are zero-padded to 8 channels)
-  for (int t0 = b0; t0 < b1; t0 += kTV) {
-    const int nv = min(kTV, b1 - t0);
-    __syncthreads();
-    if (tid < nv) {
-      sxv[tid] = conv3_neighbour(t0 + tid, tap, D);
-      szv[tid] = t0 + tid;
-    }
-    __syncthreads();
-    for (int e = tid; e < nv * (gz + gx); e += kNT) {
-      const int v = e / (gz + gx), q = e % (gz + gx);
-      if (q < gz) {
-        const bf16x8 u = *reinterpret_cast<const bf16x8*>(dz.p + static_cast<size_t>(szv[v]) * dz.ld + dz.off + 8 * q);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) sdz[v * kMaxC + 8 * q + j] = f(u[j]);
-      } else {
-        const int qq = q - gz;
-        const bf16x8 u = *reinterpret_cast<const bf16x8*>(x.p + static_cast<size_t>(sxv[v]) * x.ld + x.off + 8 * qq);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) sx[v * kMaxC + 8 * qq + j] = f(u[j]);
-      }
-    }
-    __syncthreads();
-    if (active) {
-      for (int v = grp; v < nv; v += G) {
-        const float z = sdz[v * kMaxC + o];
-        const float* xp = sx + v * kMaxC + cb * CI;
-#pragma unroll
-        for (int c = 0; c < CI; ++c) acc[c] += z * xp[c];
-        accb += z;
-      }
-    }
-  }
-  // reduce the thread groups one after another into the (no longer needed) staging buffers
-  __syncthreads();
-  float* red = sx;
-  const int slice = npb * CI;
-  for (int gg = 0; gg < G; ++gg) {
-    if (active && grp == gg) {
-#pragma unroll
-      for (int c = 0; c < CI; ++c) red[pb * CI + c] = (gg == 0 ? 0.f : red[pb * CI + c]) + acc[c];
-      sdz[pb] = (gg == 0 ? 0.f : sdz[pb]) + accb;
-    }
-    __syncthreads();
-  }
-  // canonical layout W[o][t][i] over the real input channels, then the bias (each (o, cb) pair summed dz[o]; take
-  // the cb == 0 one)
-  const int nW = cout * ntap * cin_real;
-  float* dst = partial + static_cast<size_t>(chunk) * (nW + cout);
-  for (int e = tid; e < slice; e += kNT) {
-    const int p = e / CI, c = e % CI;
-    const int oo = p / ncb, ci = (p % ncb) * CI + c;
-    if (ci < cin_real) dst[(oo * ntap + tap) * cin_real + ci] = red[e];
-  }
-  if (tap == 0)
-    for (int e = tid; e < cout; e += kNT) dst[nW + e] = sdz[e * ncb];
-}
-
-// Weight gradient of a 3^3 layer on v_mfma_f32_16x16x32_bf16, for D a multiple of 32: dW[o][t][i] =
+// Weight gradient of a 3^3 layer on v_mfma_f32_16x16x32_bf16: dW[o][t][i] =
 // sum_p dz[p][o] x[p + d_t][i] is a product whose k index is the voxel p. A workgroup takes one 16 (o) x 16 (i) tile
 // of all 27 taps over a range of bricks of 4 x 4 x 32 output voxels. Per brick it stages dz (16 rows of 32 z) and the
 // periodic x halo (6 x 6 rows of 34 z) in LDS channel-major with z contiguous, two BF16 of neighbouring z per dword,
@@ -480,7 +387,10 @@ __global__ __launch_bounds__(kNT) void k_wgrad(View x, int cin, int cin_real, Vi
 // elements) is applied in registers: the lane reads halo z 8 g .. 8 g + 9 once per (x, y) offset and takes its 8
 // values by dword selection (offsets 0 and 2) or a 16-bit funnel shift (offset 1), so the three z taps share the
 // reads. Wave w takes the brick rows at x = x0 + w (y = y0 + 0..3) and holds all 27 16 x 16 FP32 tiles; the four waves
-// and, for the bias, the four lane groups are summed in a fixed order at the end.
+// and, for the bias, the four lane groups are summed in a fixed order at the end. Bricks that reach past the grid hold
+// zeros there, so any D takes this kernel. (Sides that are no multiple of 32 used to run on the vector ALUs, one voxel
+// product per lane, and took most of a training step: one loss and gradient at 32^3 966 -> 538 us, at 64^3 1171 -> 755, at
+// 72^3 2943 -> 927; at 8^3, nearly all padding, 472 -> 484.)
 constexpr int kWB = 32;                    // z extent of a brick: one K step
 constexpr int kWRow = 20;                  // halo row pitch in dwords (17 used; a multiple of 4 for 16-byte reads)
 constexpr int kWXC = 36 * kWRow + 20;      // halo channel pitch in dwords, = 4 mod 32: 8 lanes' 16-byte reads hit
@@ -494,8 +404,6 @@ __device__ __forceinline__ unsigned half16(const u32x4& w, int j) {
 __device__ __forceinline__ unsigned funnel16(unsigned lo, unsigned hi) { return (lo >> 16) | (hi << 16); }
 __device__ __forceinline__ float bf16_bits(unsigned h) { return __uint_as_float(h << 16); }
 
-bool wgrad3_mfma(int kind, int D) { return kind == 0 && D >= kWB && D % kWB == 0; }
-
 __global__ __launch_bounds__(kNT, 2) void k_wgrad3(View x, int cin, int cin_real, View dz, int cout, int D, int nchunk,
                                                    float* __restrict__ partial) {
   __shared__ __attribute__((aligned(16))) unsigned sx[16 * kWXC];
@@ -506,7 +414,7 @@ __global__ __launch_bounds__(kNT, 2) void k_wgrad3(View x, int cin, int cin_real
   const int nib = (cin + 15) / 16;
   const int ob = blockIdx.y / nib, ib = blockIdx.y % nib;
   const int coutp = (cout + 7) & ~7;
-  const int nb4 = D / 4, nbz = D / kWB;
+  const int nb4 = (D + 3) / 4, nbz = (D + kWB - 1) / kWB;
   const int nbrick = nb4 * nb4 * nbz;
   const int per = (nbrick + nchunk - 1) / nchunk;
   const int k0 = per * chunk, k1 = min(nbrick, k0 + per);
@@ -529,10 +437,11 @@ __global__ __launch_bounds__(kNT, 2) void k_wgrad3(View x, int cin, int cin_real
       const int q = e >> 8, r = (e >> 4) & 15, p = e & 15;
       const int ch = 16 * ob + 8 * q;
       rz[m][0] = rz[m][1] = u32x4{0u, 0u, 0u, 0u};
-      if (ch < coutp) {  // channels at or past coutp stay zero
+      // channels at or past coutp and voxels past the grid's edge stay zero
+      if (ch < coutp && x0 + (r >> 2) < D && y0 + (r & 3) < D && z0 + 2 * p < D) {
         const size_t vox = (static_cast<size_t>(x0 + (r >> 2)) * D + (y0 + (r & 3))) * D + z0 + 2 * p;
         rz[m][0] = *reinterpret_cast<const u32x4*>(dz.p + vox * dz.ld + dz.off + ch);
-        rz[m][1] = *reinterpret_cast<const u32x4*>(dz.p + (vox + 1) * dz.ld + dz.off + ch);
+        if (z0 + 2 * p + 1 < D) rz[m][1] = *reinterpret_cast<const u32x4*>(dz.p + (vox + 1) * dz.ld + dz.off + ch);
       }
     }
 #pragma unroll
@@ -542,12 +451,15 @@ __global__ __launch_bounds__(kNT, 2) void k_wgrad3(View x, int cin, int cin_real
       if (e < kHI) {
         const int q = e / (36 * 17), rem = e - q * (36 * 17), hr = rem / 17, p = rem - hr * 17;
         const int ch = 16 * ib + 8 * q;
-        if (ch < cin) {
-          const int gx = wrapi(x0 - 1 + hr / 6, D), gy = wrapi(y0 - 1 + hr % 6, D);
+        // halo voxels past the periodic image of the first one (index D) meet only zeros of dz and stay zero
+        const int hx = x0 - 1 + hr / 6, hy = y0 - 1 + hr % 6, hz = z0 - 1 + 2 * p;
+        if (ch < cin && hx <= D && hy <= D) {
+          const int gx = wrapi(hx, D), gy = wrapi(hy, D);
           const size_t row = (static_cast<size_t>(gx) * D + gy) * D;
-          const size_t v0 = row + wrapi(z0 - 1 + 2 * p, D), v1 = row + wrapi(z0 + 2 * p, D);
-          rh[m][0] = *reinterpret_cast<const u32x4*>(x.p + v0 * x.ld + x.off + ch);
-          rh[m][1] = *reinterpret_cast<const u32x4*>(x.p + v1 * x.ld + x.off + ch);
+          if (hz <= D)
+            rh[m][0] = *reinterpret_cast<const u32x4*>(x.p + (row + wrapi(hz, D)) * x.ld + x.off + ch);
+          if (hz < D)
+            rh[m][1] = *reinterpret_cast<const u32x4*>(x.p + (row + wrapi(hz + 1, D)) * x.ld + x.off + ch);
         }
       }
     }
@@ -1029,33 +941,19 @@ hipError_t transpose2(const float* W, int cout, int cin, float* Wt, hipStream_t 
 int wgrad_chunks(int kind, int cin, int cout, int D) {
   const int ntile = ((cout + 15) / 16) * ((cin + 15) / 16);
   const int c512 = std::max(1, 512 / ntile);  // about 512 workgroups over the chunks and the (o, i) tiles
-  if (wgrad3_mfma(kind, D)) return std::min(c512, (D / 4) * (D / 4) * (D / kWB));
-  if (kind != 0) {
-    const int Dc = (kind == 1) ? D / 2 : D;
-    return std::min(c512, (Dc * Dc * Dc + kW2Y - 1) / kW2Y);
-  }
-  const int c = D * D * D / 4096;  // 3^3 layer on the VALU kernel
-  return c < 1 ? 1 : (c > 64 ? 64 : c);
+  if (kind == 0) return std::min(c512, ((D + 3) / 4) * ((D + 3) / 4) * ((D + kWB - 1) / kWB));
+  const int Dc = (kind == 1) ? D / 2 : D;
+  return std::min(c512, (Dc * Dc * Dc + kW2Y - 1) / kW2Y);
 }
 
 hipError_t wgrad(int kind, View x, int cin, int cin_real, View dz, int cout, int D, float* partial, hipStream_t s) {
   if (cin > kMaxC || cout > kMaxC || (cin % 8) != 0) return hipErrorInvalidValue;
-  if (wgrad3_mfma(kind, D) || kind != 0) {
-    const int nchunk = wgrad_chunks(kind, cin, cout, D);
-    const dim3 grid(static_cast<unsigned>(nchunk), static_cast<unsigned>(((cout + 15) / 16) * ((cin + 15) / 16)));
-    if (kind == 0)
-      k_wgrad3<<<grid, kNT, 0, s>>>(x, cin, cin_real, dz, cout, D, nchunk, partial);
-    else
-      k_wgrad2<<<grid, kNT, 0, s>>>(kind, x, cin, cin_real, dz, cout, D, nchunk, partial);
-    return hipGetLastError();
-  }
-  const dim3 grid(static_cast<unsigned>(wgrad_chunks(kind, cin, cout, D)), 27u);  // a 3^3 layer on a small grid
-  if (cin == 8)
-    k_wgrad<8><<<grid, kNT, 0, s>>>(x, cin, cin_real, dz, cout, D, partial);
-  else if ((cin % 16) == 0 && cout * (cin / 16) <= kNT)
-    k_wgrad<16><<<grid, kNT, 0, s>>>(x, cin, cin_real, dz, cout, D, partial);
+  const int nchunk = wgrad_chunks(kind, cin, cout, D);
+  const dim3 grid(static_cast<unsigned>(nchunk), static_cast<unsigned>(((cout + 15) / 16) * ((cin + 15) / 16)));
+  if (kind == 0)
+    k_wgrad3<<<grid, kNT, 0, s>>>(x, cin, cin_real, dz, cout, D, nchunk, partial);
   else
-    return hipErrorInvalidValue;
+    k_wgrad2<<<grid, kNT, 0, s>>>(kind, x, cin, cin_real, dz, cout, D, nchunk, partial);
   return hipGetLastError();
 }
 
