@@ -376,10 +376,15 @@ class JobPack {
   Section add(const std::vector<J>& jobs, const std::vector<int>& items) {
     Section s;
     s.njob = static_cast<int>(jobs.size());
-    std::vector<int> offs(jobs.size() + 1, 0);
-    for (size_t i = 0; i < jobs.size(); ++i) offs[i + 1] = offs[i] + round8(items[i]);
-    s.total = offs.back();
     s.jobs_off = append(jobs.data(), jobs.size() * sizeof(J));
+    return with_items(s, items);
+  }
+  // The jobs of section s, not stored again, under another item table. (A batch fills the job region with 2 KB a box: what
+  // a box takes here is what limits the boxes of a call.)
+  Section with_items(Section s, const std::vector<int>& items) {
+    std::vector<int> offs(items.size() + 1, 0);
+    for (size_t i = 0; i < items.size(); ++i) offs[i + 1] = offs[i] + round8(items[i]);
+    s.total = offs.back();
     s.offs_off = append(offs.data(), offs.size() * sizeof(int));
     return s;
   }
@@ -868,7 +873,7 @@ ForceProgram add_force(JobPack& jp, const std::vector<ForceBox>& boxes, const So
     if (cola_run) f.sort_next[c] = jp.add(sn[c], i_part);
     f.dep[c] = jp.add(dj[c], i_tile);
     f.parts[c] = jp.add(pj[c], i_part);
-    f.frame[c] = jp.add(pj[c], i_frame);
+    f.frame[c] = jp.with_items(f.parts[c], i_frame);
     f.unsort[c] = jp.add(uj[c], i_part);
   }
   f.zr2c = jp.add(zs, i_z);
