@@ -175,11 +175,23 @@ __device__ __forceinline__ void fft_tile_fixed(float2* tile, const float2* tw, c
   }
 }
 
+// i, with HIDE as a value that the compiler does not know: indices formed from it are not kept in registers from one phase
+// to the next.
+template <bool HIDE>
+__device__ __forceinline__ int opaque(int i) {
+  if constexpr (HIDE) asm volatile("" : "+v"(i));
+  return i;
+}
+
 // The x pass. A tile is B columns (kz) of one ky. delta(k) = wbase base + sum_i w_i FFT_x(in_i), zero at k = 0 and on
 // the Nyquist planes, stays in the threads' registers (thread (j0, b) owns rows j0 + m S, S = kFftNT / B); each output
 // is the inverse x transform of a factor times it. A workgroup reads and writes its own columns only, so the outputs may
 // be the inputs' buffers.
-template <int B, int M>
+// SUM: delta has more than one term. The sum is formed in FP64 and rounded once, since the terms of a non-Gaussian field may
+// exceed it by far. An instance of its own: its accumulators live through the transforms, and only without the indices that
+// the compiler would carry along does it keep the register cap (160^3 equilateral, the three x passes: sum in FP32 147 us,
+// in FP64 with 15 spilled registers 161, without a cap 191, so 149; the single-term instance is 1.5 % slower that way).
+template <int B, int M, bool SUM>
 __global__ __launch_bounds__(kFftNT, M <= 8 ? 4 : 2) void k_ic_x(IcX a) {
   constexpr int BP = strided_pitch(B), S = kFftNT / B;
   extern __shared__ float2 smem[];
@@ -195,47 +207,63 @@ __global__ __launch_bounds__(kFftNT, M <= 8 ? 4 : 2) void k_ic_x(IcX a) {
   const int ny = y <= half ? y : y - n, nyz2 = ny * ny + nz * nz;
   const TableRegs<float2> r_tw = table_load(a.tw, n, tid);
   float2 d[M];
+  double sx[SUM ? M : 1], sy[SUM ? M : 1];
+  if constexpr (SUM) {
 #pragma unroll
-  for (int m = 0; m < M; ++m) d[m] = make_float2(0.f, 0.f);
+    for (int m = 0; m < M; ++m) sx[m] = sy[m] = 0.0;
+  }
+  auto add = [&](int m, float2 v, double w) {
+    if constexpr (SUM) {
+      sx[m] += v.x * w;
+      sy[m] += v.y * w;
+    } else {
+      d[m] = make_float2(static_cast<float>(v.x * w), static_cast<float>(v.y * w));
+    }
+  };
   auto mode2 = [&](int j) {  // |n|^2 of row j, 0 for a dropped mode
     const int nx = j <= half ? j : j - n;
     return (col && nx != half && ny != half) ? nx * nx + nyz2 : 0;
   };
-  if (a.base) {
+  table_store(tw, r_tw, n, tid);
+  for (int i = 0; i < a.nin; ++i) {
+    const float2* in = a.in[i];
+    const int j2 = opaque<SUM>(j0);
+    float2 v[M];
+#pragma unroll
+    for (int m = 0; m < M; ++m) v[m] = in[off + static_cast<uint32_t>(min(j2 + m * S, n - 1)) * astr];
+#pragma unroll
+    for (int m = 0; m < M; ++m)
+      if (j2 + m * S < n) tile[(j2 + m * S) * BP + b] = v[m];
+    __syncthreads();
+    fft_tile_fixed<false, M, B, BP>(tile, tw, a.pl, tid);
+    const double* w = a.w[i];
+    const int j1 = opaque<SUM>(j0);
 #pragma unroll
     for (int m = 0; m < M; ++m) {
-      const int j = j0 + m * S;
+      const int j = j1 + m * S;
+      if (j < n) {
+        const float2 x = tile[j * BP + b];
+        const int n2 = mode2(j);
+        add(m, x, w ? w[n2] : (n2 ? 1.0 : 0.0));
+      }
+    }
+  }
+  if (a.base) {
+    const int j1 = opaque<SUM>(j0);
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+      const int j = j1 + m * S;
       if (j < n) {
         const float2 v = a.base[off + static_cast<uint32_t>(j) * astr];
         const int n2 = mode2(j);
         const double w = a.wbase ? a.wbase[n2] : (n2 ? 1.0 : 0.0);
-        d[m] = make_float2(static_cast<float>(v.x * w), static_cast<float>(v.y * w));
+        add(m, v, w);
       }
     }
   }
-  table_store(tw, r_tw, n, tid);
-  for (int i = 0; i < a.nin; ++i) {
-    const float2* in = a.in[i];
-    float2 v[M];
+  if constexpr (SUM) {
 #pragma unroll
-    for (int m = 0; m < M; ++m) v[m] = in[off + static_cast<uint32_t>(min(j0 + m * S, n - 1)) * astr];
-#pragma unroll
-    for (int m = 0; m < M; ++m)
-      if (j0 + m * S < n) tile[(j0 + m * S) * BP + b] = v[m];
-    __syncthreads();
-    fft_tile_fixed<false, M, B, BP>(tile, tw, a.pl, tid);
-    const double* w = a.w[i];
-#pragma unroll
-    for (int m = 0; m < M; ++m) {
-      const int j = j0 + m * S;
-      if (j < n) {
-        const float2 x = tile[j * BP + b];
-        const int n2 = mode2(j);
-        const double f = w ? w[n2] : (n2 ? 1.0 : 0.0);
-        d[m].x += static_cast<float>(x.x * f);
-        d[m].y += static_cast<float>(x.y * f);
-      }
-    }
+    for (int m = 0; m < M; ++m) d[m] = make_float2(static_cast<float>(sx[m]), static_cast<float>(sy[m]));
   }
   if (a.keep) {
 #pragma unroll
@@ -246,9 +274,10 @@ __global__ __launch_bounds__(kFftNT, M <= 8 ? 4 : 2) void k_ic_x(IcX a) {
   for (int o = 0; o < a.nout; ++o) {
     const int kind = a.kind[o];
     const double* w = a.wout[o];
+    const int j1 = opaque<SUM>(j0);
 #pragma unroll
     for (int m = 0; m < M; ++m) {
-      const int j = j0 + m * S;
+      const int j = j1 + m * S;
       if (j < n) {
         const int n2 = mode2(j);
         const float kx = kf * static_cast<float>(j <= half ? j : j - n);
@@ -269,9 +298,10 @@ __global__ __launch_bounds__(kFftNT, M <= 8 ? 4 : 2) void k_ic_x(IcX a) {
     __syncthreads();
     fft_tile_fixed<true, M, B, BP>(tile, tw, a.pl, tid);
     float2* out = a.out[o];
+    const int j2 = opaque<SUM>(j0);
 #pragma unroll
     for (int m = 0; m < M; ++m)
-      if (j0 + m * S < n && col) out[off + static_cast<uint32_t>(j0 + m * S) * astr] = tile[(j0 + m * S) * BP + b];
+      if (j2 + m * S < n && col) out[off + static_cast<uint32_t>(j2 + m * S) * astr] = tile[(j2 + m * S) * BP + b];
   }
 }
 
@@ -524,9 +554,12 @@ struct IcInit {
     big_lds(k_ic_r2c<false, 8>);
     big_lds(k_ic_r2c<false, 16>);
     big_lds(k_ic_r2c<false, 32>);
-    big_lds(k_ic_x<16, 8>);
-    big_lds(k_ic_x<8, 8>);
-    big_lds(k_ic_x<8, 16>);
+    big_lds(k_ic_x<16, 8, false>);
+    big_lds(k_ic_x<16, 8, true>);
+    big_lds(k_ic_x<8, 8, false>);
+    big_lds(k_ic_x<8, 8, true>);
+    big_lds(k_ic_x<8, 16, false>);
+    big_lds(k_ic_x<8, 16, true>);
     big_lds(k_ic_y<16, 8>);
     big_lds(k_ic_y<8, 8>);
     big_lds(k_ic_y<8, 16>);
@@ -592,9 +625,17 @@ hipError_t ic_x(IcX a, hipStream_t s) {
   a.ntc = (a.N / 2 + B - 1) / B;
   const unsigned grid = static_cast<unsigned>(a.N * a.ntc);
   const size_t lds = ic_cols_lds(a.N);
-  if (B == 16) k_ic_x<16, 8><<<grid, kFftNT, lds, s>>>(a);
-  else if (a.N <= 512) k_ic_x<8, 8><<<grid, kFftNT, lds, s>>>(a);
-  else k_ic_x<8, 16><<<grid, kFftNT, lds, s>>>(a);
+  const int terms = a.nin + (a.base ? 1 : 0);
+  if (terms < 1) return hipErrorInvalidValue;
+#define LPC_IC_X(BB, MM)                                                  \
+  {                                                                       \
+    if (terms > 1) k_ic_x<BB, MM, true><<<grid, kFftNT, lds, s>>>(a);     \
+    else k_ic_x<BB, MM, false><<<grid, kFftNT, lds, s>>>(a);              \
+  }
+  if (B == 16) LPC_IC_X(16, 8)
+  else if (a.N <= 512) LPC_IC_X(8, 8)
+  else LPC_IC_X(8, 16)
+#undef LPC_IC_X
   return hipGetLastError();
 }
 
