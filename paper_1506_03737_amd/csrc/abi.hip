@@ -610,8 +610,8 @@ struct ForceBox {
 struct ForceProgram {
   // sorting: user -> copy 0; copy c -> copy 1 - c; per-copy particle stages
   Section sort_user, sort_next[2], dep[2], parts[2], frame[2], unsort[2];
-  Section zr2c, yfwd, yinv, zc2r;
-  int Bz = 32, Bax = 32, R3 = 16;
+  Section zr2c, yfwd, yinv;
+  int Bz = 32, Bax = 32;
   // The fused x pass of the boxes whose transforms chain through registers (plan 8 x 8 x R or 4 x 4 x 8 x 8 and 8 columns)
   // and of the others: two launches, so that a box takes the form that it takes by itself.
   struct Pois {
@@ -619,10 +619,18 @@ struct ForceProgram {
     int B = 16, M = 8;  // the narrowest width and the most points per thread over the boxes
     size_t lds = 0;
   } pois[2];  // [1]: chained
-  int P3 = 8;  // points per thread of the three-spectrum c2r tiles: the largest over the boxes
+  // The three-spectrum c2r pass, by rows per tile: one launch for the boxes of each width. (At the narrowest width of the
+  // batch, 48 boxes of 192, 256 and 320 took 5.6 ms per evaluation with the largest tuned to 4 rows, now 4.75; 30 of 128 and
+  // one of 512 at the built-in widths 1.35 ms, now 0.95.)
+  struct C2R {
+    Section sec;
+    int P = 8;  // points per thread: the largest over the boxes
+    size_t lds = 0;
+  };
+  std::map<int, C2R> c2r;
   int Pax = 8;  // points per thread of the strided y tiles: the largest over the boxes
   int Pz = 8;   // points per thread of the forward z tiles: the largest over the boxes
-  size_t lds_z = 0, lds_ax = 0, lds_c = 0;
+  size_t lds_z = 0, lds_ax = 0;
   SortSpace ss;
   bool cola_run = false;
   bool fixed = true;      // every box's strided passes have compiled plans
@@ -673,22 +681,24 @@ ForceProgram add_force(JobPack& jp, const std::vector<ForceBox>& boxes, const So
   f.ss = ss;
   f.cola_run = cola_run;
   for (const ForceBox& b : boxes) f.fixed_in |= b.keep_counts;
-  std::vector<int> chained;  // per box (another thread may set a tiling meanwhile: it is read once)
+  std::vector<int> chained, rows;  // per box (another thread may set a tiling meanwhile: it is read once)
   for (const ForceBox& b : boxes) {
-    // widths fit every smaller size too, so the smallest over the boxes fits all of them
+    // widths fit every smaller size too, so the smallest over the boxes fits all of them (c2r: each its own)
     const lpc_fft_tiling t = tiling_of(b.nm);
     f.Bz = std::min(f.Bz, t.z_rows);
     f.Bax = std::min(f.Bax, t.axis_cols);
     chained.push_back(t.poisson_cols == 8 && kern::poisson_chainable(plan_of(b.nm)));
     int& Bp = f.pois[chained.back()].B;
     Bp = std::min(Bp, t.poisson_cols);
-    f.R3 = std::min(f.R3, t.c2r_rows);
+    rows.push_back(t.c2r_rows);
   }
   for (size_t ib = 0; ib < boxes.size(); ++ib) {
     const ForceBox& b = boxes[ib];
     ForceProgram::Pois& fp = f.pois[chained[ib]];
     fp.M = std::max(fp.M, kern::poisson_points(b.nm, fp.B));
-    f.P3 = std::max(f.P3, kern::c2r_points(b.nm, f.R3));
+    ForceProgram::C2R& fc = f.c2r[rows[ib]];
+    fc.P = std::max(fc.P, kern::c2r_points(b.nm, rows[ib]));
+    fc.lds = std::max(fc.lds, kern::lds_z_c2r(b.nm, 3 * rows[ib]));
     f.Pax = std::max(f.Pax, kern::axis_points(b.nm, f.Bax));
     f.Pz = std::max(f.Pz, kern::r2c_points(b.nm, f.Bz));
     f.fixed = f.fixed && kern::has_fixed_plan(y_plan_of(b.nm));
@@ -702,8 +712,9 @@ ForceProgram add_force(JobPack& jp, const std::vector<ForceBox>& boxes, const So
   std::vector<kern::AxisJob> ys;
   std::vector<kern::YGradJob> yis;
   std::vector<kern::PoissonJob> ps[2];
-  std::vector<kern::ZC2RJob> cs;
-  std::vector<int> i_part, i_frame, i_tile, i_z, i_y, i_yi, i_p[2], i_c;
+  std::map<int, std::vector<kern::ZC2RJob>> cs;
+  std::map<int, std::vector<int>> i_c;
+  std::vector<int> i_part, i_frame, i_tile, i_z, i_y, i_yi, i_p[2];
   for (size_t ib = 0; ib < boxes.size(); ++ib) {
     const ForceBox& b = boxes[ib];
     const int nm = b.nm, pitch = kern::mesh_pitch(nm), nh = nm / 2 + 1;
@@ -861,12 +872,11 @@ ForceProgram add_force(JobPack& jp, const std::vector<ForceBox>& boxes, const So
     c.pl = plan_of(nm / 2, false);
     c.tw = jp.twiddles(c.pl);
     c.roots = jp.half_roots(nm);
-    cs.push_back(c);
-    i_c.push_back((c.nrows + f.R3 - 1) / f.R3);
+    cs[rows[ib]].push_back(c);
+    i_c[rows[ib]].push_back((c.nrows + rows[ib] - 1) / rows[ib]);
     f.lds_z = std::max(f.lds_z, kern::lds_z_r2c(nm, f.Bz));
     f.lds_ax = std::max(f.lds_ax, kern::lds_axis(nm, f.Bax));
     fp.lds = std::max(fp.lds, kern::lds_x_poisson(nm, fp.B, fp.M, ch != 0));
-    f.lds_c = std::max(f.lds_c, kern::lds_z_c2r(nm, 3 * f.R3));
   }
   f.sort_user = jp.add(su, i_part);
   for (int c = 0; c < ncopy; ++c) {
@@ -881,7 +891,7 @@ ForceProgram add_force(JobPack& jp, const std::vector<ForceBox>& boxes, const So
   for (int ch = 0; ch < 2; ++ch)
     if (!ps[ch].empty()) f.pois[ch].sec = jp.add(ps[ch], i_p[ch]);
   f.yinv = jp.add(yis, i_yi);
-  f.zc2r = jp.add(cs, i_c);
+  for (auto& [r, fc] : f.c2r) fc.sec = jp.add(cs[r], i_c[r]);
   return f;
 }
 
@@ -920,7 +930,11 @@ void run_force_mesh(const JobPack& jp, const ForceProgram& f, int c, int* flags,
     stage("fft x + poisson", s, [&] { return kern::launch_poisson(jp.jobs<kern::PoissonJob>(fp.sec), jp.table(fp.sec), fp.B, fp.M, ch != 0, fp.lds, s); });
   }
   stage("fft y inv", s, [&] { return kern::launch_y_grad(jp.jobs<kern::YGradJob>(f.yinv), jp.table(f.yinv), f.Bax, f.Pax, f.fixed, f.lds_ax, s); });
-  stage("fft z c2r", s, [&] { return kern::launch_z_c2r(jp.jobs<kern::ZC2RJob>(f.zc2r), jp.table(f.zc2r), 3, f.R3, f.P3, f.lds_c, s); });
+  for (const auto& [r, fc] : f.c2r) {
+    const int R = r;
+    const ForceProgram::C2R& g = fc;
+    stage("fft z c2r", s, [&] { return kern::launch_z_c2r(jp.jobs<kern::ZC2RJob>(g.sec), jp.table(g.sec), 3, R, g.P, g.lds, s); });
+  }
 }
 
 // The whole COLA run over a_list for every box (all boxes share cosmology, stepping and time list). Particles are
