@@ -528,7 +528,7 @@ R2CSections add_r2c(JobPack& jp, const void* in, bool fixed, double mscale, int 
   r.Pz = kern::r2c_points(n, r.Bz);
   r.lds_z = kern::lds_z_r2c(n, r.Bz);
   r.lds_ax = kern::lds_axis(n, r.Bax);
-  r.fixed = kern::has_fixed_plan(plan_of(n));
+  r.fixed = kern::has_fixed_plan(plan_of(n), r.Bax, r.Pax);
   kern::ZR2CJob z{};
   z.in = in;
   z.out = out;
@@ -556,7 +556,7 @@ C2RSections add_c2r(JobPack& jp, float2* spec, int n, float* out, float scale) {
   c.R = t.z_rows;
   c.Pax = kern::axis_points(n, c.Bax);
   c.lds_ax = kern::lds_axis(n, c.Bax);
-  c.fixed = kern::has_fixed_plan(plan_of(n));
+  c.fixed = kern::has_fixed_plan(plan_of(n), c.Bax, c.Pax);
   c.lds_z = kern::lds_z_c2r(n, c.R);
   kern::AxisJob x = axis_job(jp, spec, n, static_cast<int64_t>(n) * pitch, pitch, 0, c.Bax);
   c.x = jp.add1(x, x.per_comp);
@@ -701,7 +701,7 @@ ForceProgram add_force(JobPack& jp, const std::vector<ForceBox>& boxes, const So
     fc.lds = std::max(fc.lds, kern::lds_z_c2r(b.nm, 3 * rows[ib]));
     f.Pax = std::max(f.Pax, kern::axis_points(b.nm, f.Bax));
     f.Pz = std::max(f.Pz, kern::r2c_points(b.nm, f.Bz));
-    f.fixed = f.fixed && kern::has_fixed_plan(y_plan_of(b.nm));
+    f.fixed = f.fixed && kern::has_fixed_plan(y_plan_of(b.nm), f.Bax, f.Pax);  // (Pax only grows)
   }
   const int ncopy = cola_run ? 2 : 1;
   std::vector<kern::SortJob> su, sn[2];
@@ -1637,7 +1637,7 @@ lpc_status init_ic_impl(const lpc_geometry* geom, const lpc_cosmology* cosmo, ui
     const float2 *tw = jp.twiddles(full), *twh = jp.twiddles(hplan), *roots = jp.half_roots(N);
     const int Bax = tiling_of(N).axis_cols, Pax = kern::axis_points(N, Bax);
     const size_t lds_ax = kern::lds_axis(N, Bax);
-    const bool fixed = kern::has_fixed_plan(full);
+    const bool fixed = kern::has_fixed_plan(full, Bax, Pax);
     // forward y pass of meshes m[0..count), without the kz = N / 2 column
     auto y_forward = [&](float2* const* m, int count) {
       std::vector<kern::AxisJob> jobs;

@@ -14,8 +14,9 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <utility>
 #include <cmath>
+#include <initializer_list>
+#include <utility>
 
 #include "fft_plans.h"
 
@@ -470,21 +471,20 @@ int poisson_points(int n, int B) {
   return pts <= 8 ? 8 : (pts <= 12 ? 12 : 16);
 }
 
-bool has_fixed_plan(const Plan1D& pl) {
-  static constexpr int kPlans[][4] = {{8, 8, 12}, {12, 8, 8}, {8, 8, 5}, {8, 8, 4}, {8, 8, 3}, {4, 4, 8, 8}, {4, 8, 12}};
-  for (const auto& p : kPlans) {
-    bool same = pl.nst == (p[3] ? 4 : 3);
-    for (int s = 0; same && s < pl.nst; ++s) same = pl.radix[s] == p[s];
-    if (same) return true;
-  }
-  return false;
+namespace {
+bool same_plan(const Plan1D& pl, std::initializer_list<int> radices) {
+  return pl.nst == static_cast<int>(radices.size()) && std::equal(radices.begin(), radices.end(), pl.radix);
+}
+}  // namespace
+
+bool has_fixed_plan(const Plan1D& pl, int B, int P) {
+#define LPC_SAME(...) same_plan(pl, {__VA_ARGS__}) ||
+  return plan_fits(pl.n, pl.nst, B, P) && (LPC_FIXED_PLANS(LPC_SAME) false);
 }
 
 bool poisson_chainable(const Plan1D& pl) {
-  if (pl.nst == 4) return pl.radix[0] == 4 && pl.radix[1] == 4 && pl.radix[2] == 8 && pl.radix[3] == 8;
-  if (pl.nst != 3 || pl.radix[0] != 8 || pl.radix[1] != 8) return false;
-  const int r = pl.radix[2];
-  return r == 12 || r == 5 || r == 4 || r == 3;
+  return plan_fits(pl.n, pl.nst, 8, poisson_points(pl.n, 8)) && (LPC_CHAINED_PLANS(LPC_SAME) false);
+#undef LPC_SAME
 }
 
 size_t lds_x_poisson(int n, int B, int M, bool chained) {

@@ -422,7 +422,7 @@ template <bool INV, int EPT, int B, int BP, int... Rs>
 struct FixedFFT {
   static constexpr int kN = (Rs * ...);
   static constexpr int kNst = sizeof...(Rs);
-  static constexpr bool kFits = kN <= EPT * (kFftNT / B) && kNst <= kMaxStages;
+  static constexpr bool kFits = plan_fits(kN, kNst, B, EPT);
   template <class PL>
   static __device__ __forceinline__ bool matches(const PL& pl) {
     if constexpr (!kFits) {

@@ -144,13 +144,7 @@ __device__ __forceinline__ void fft_io_fast(float2* tile, const float2* tw, cons
   if (try_fixed_io<FixedFFT<INV, EPT, B, BP, __VA_ARGS__>, PL, GIN, GOUT, PAIRS>(tile, tw, pl, tid, load, pair, mid, \
                                                                              store))                             \
     return;
-  LPC_TRY_IO(8, 8, 12)
-  LPC_TRY_IO(12, 8, 8)    // 768 in the force's y passes
-  LPC_TRY_IO(8, 8, 5)
-  LPC_TRY_IO(8, 8, 4)
-  LPC_TRY_IO(8, 8, 3)
-  LPC_TRY_IO(4, 4, 8, 8)  // 1024: the large box
-  LPC_TRY_IO(4, 8, 12)    // 384: the learned form's fine training runs
+  LPC_FIXED_PLANS(LPC_TRY_IO)
 #undef LPC_TRY_IO
   if constexpr (RT)
     fft_io_runtime<INV, EPT, B, BP, GIN, GOUT, PAIRS>(tile, tw, pl, tid, load, pair, mid, store);

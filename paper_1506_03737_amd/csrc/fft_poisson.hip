@@ -176,11 +176,7 @@ __global__ __launch_bounds__(kFftNT, (CHAIN && M <= 8) ? 6 : ((CHAIN || M <= 12)
       };
 #define LPC_CHAIN(...) \
   if (x_poisson_chained<M, __VA_ARGS__>(tile, tw, r_twr, J.pl, tid, load, mid, make_factor, store_a, store_c)) return;
-      LPC_CHAIN(8, 8, 12)
-      LPC_CHAIN(8, 8, 5)
-      LPC_CHAIN(8, 8, 4)
-      LPC_CHAIN(8, 8, 3)
-      LPC_CHAIN(4, 4, 8, 8)
+      LPC_CHAINED_PLANS(LPC_CHAIN)
 #undef LPC_CHAIN
       return;
     } else {

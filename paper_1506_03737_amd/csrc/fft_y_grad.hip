@@ -19,7 +19,7 @@ namespace {
 template <int B, int EPT, bool RT>
 __global__ __launch_bounds__(kFftNT, EPT <= 8 ? 6 : 4) void k_fft_y_grad(
     const YGradJob* __restrict__ jobs, const int* __restrict__ offs, int njob, int total) {
-  constexpr int BP = strided_pitch(B), H = EPT / 2, BH = B / 2;
+  constexpr int BP = strided_pitch(B), BH = B / 2;
   extern __shared__ float2 smem[];
   const int w = blockIdx.x;
   const int tid = threadIdx.x;

@@ -318,15 +318,29 @@ hipError_t launch_z_r2c(const ZR2CJob* jobs, WorkTable wt, bool fixed, int B, in
 void init_axis();
 void init_y_grad();
 void init_poisson();
-// fixed_plans: every job's plan is one that the strided passes carry compiled (has_fixed_plan)
-bool has_fixed_plan(const Plan1D& pl);
+// The plans that the strided passes carry compiled, and those whose fused x pass chains its transforms through registers:
+// the kernels and the host's choice of an instance expand the same lists, and test the fit with the same rule (an instance
+// without run-time stages leaves a plan that it does not carry untransformed).
+#define LPC_FIXED_PLANS(X)                                                  \
+  X(8, 8, 12)                                                               \
+  X(12, 8, 8) /* 768 in the force's y passes */                             \
+  X(8, 8, 5)                                                                \
+  X(8, 8, 4)                                                                \
+  X(8, 8, 3)                                                                \
+  X(4, 4, 8, 8) /* 1024: the large box */                                   \
+  X(4, 8, 12)   /* 384: the learned form's fine training runs */
+#define LPC_CHAINED_PLANS(X) X(8, 8, 12) X(8, 8, 5) X(8, 8, 4) X(8, 8, 3) X(4, 4, 8, 8)
+// Whether a plan of length n runs on tiles of B columns with P points per thread.
+constexpr bool plan_fits(int n, int nst, int B, int P) { return n <= P * (kFftNT / B) && nst <= kMaxStages; }
+// fixed_plans: every job's plan is one that the strided passes carry compiled and fits their tile (has_fixed_plan)
+bool has_fixed_plan(const Plan1D& pl, int B, int P);
 hipError_t launch_axis(const AxisJob* jobs, WorkTable wt, bool inverse, int B, int P, bool fixed_plans, size_t lds,
                        hipStream_t s);
 hipError_t launch_y_grad(const YGradJob* jobs, WorkTable wt, int B, int P, bool fixed_plans, size_t lds, hipStream_t s);
 // chained: every job's plan is poisson_chainable and B = 8 (the transforms chained through registers)
 hipError_t launch_poisson(const PoissonJob* jobs, WorkTable wt, int B, int M, bool chained, size_t lds, hipStream_t s);
-// Plans 8 x 8 x R with R in {12, 5, 4, 3}, and 4 x 4 x 8 x 8: the fused x pass can chain its transforms through
-// registers.
+// Whether the fused x pass can chain the plan's transforms through registers (LPC_CHAINED_PLANS, on 8-column tiles; at
+// the points per thread that poisson_points gives, every such plan fits).
 bool poisson_chainable(const Plan1D& pl);
 hipError_t launch_z_c2r(const ZC2RJob* jobs, WorkTable wt, int nc, int R, int P, size_t lds, hipStream_t s);
 
