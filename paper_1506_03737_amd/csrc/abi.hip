@@ -638,8 +638,10 @@ struct ForceProgram {
   int* split_count = nullptr;  // a single box whose heavy tiles the deposit may split
 };
 
-// Particles of a box from which its heaviest tiles may be split: below, no tile can hold so many that the launch of the
-// chunks' kernel (5 us) would be won back.
+// Particles of a box from which its heaviest tiles may be split. The chunks' kernel and the marking cost every set 3 to 7 us,
+// also one with nothing to split, which counts in the small boxes' calls (uniform sets on 64^3: 16384 particles 115 -> 122 us,
+// 65536 140 -> 146, 131072 178 -> 186). A smaller set gains only if one tile holds most of it: with 90 % of the particles in
+// one clump the call goes from 150 to 145 us at 16384, 263 -> 167 at 65536, 564 -> 176 at 100000, 725 -> 187 at 131072.
 constexpr int64_t kSplitMin = 1 << 17;
 
 // Slots and list for splitting the heavy tiles of a box of n particles in the spare bytes [base, base + bytes) (free from
@@ -669,7 +671,11 @@ kern::DepSplit dep_split(char* base, size_t bytes, const kern::TileGrid& nt, int
   sp.slots = static_cast<int>(std::min<size_t>(slots, 1 << 20));
   sp.entries = static_cast<int>(std::min<size_t>(entries, 1 << 28));
   // Chunks of 4096 particles (16 per thread). The chunks' kernel runs before the whole tiles', so a tile is split only when
-  // it would outlast them: four times the mean (a uniform tile is reached by 1.4 times its own particles), 8192 at least.
+  // it would outlast them: four times a tile's mean share, 8192 at least. (What counts is the particles that reach a tile,
+  // its own and the boundary buckets of seven neighbours: 1 + 7 (1 - 15 7 31 / 4096) = 2.4 shares of a uniform set, so the
+  // trigger is 1.6 times a uniform tile.) Deposit with 4, 6 and 10 shares: 4 M particles, half of them in 200 clumps, on
+  // 128^3 146, 160 and 382 us (unsplit 764); 16 M on 256^3 796, 650 and 584 (3016); 256^3 of a = 1 on 128^3, which has
+  // nothing to split, 470, 469 and 469 (464).
   sp.size = 4096;
   sp.trigger = static_cast<int>(std::min<int64_t>(INT32_MAX, std::max<int64_t>(8192, 4 * n / nt.count())));
   return sp;
