@@ -238,11 +238,13 @@ __global__ __launch_bounds__(kNT) void k_tile_key(const SortJob* __restrict__ jo
 }
 
 // Exclusive scan of cnt[0..count) into start[0..count], which also zeroes cnt for the next key pass (one launch fewer per
-// sort). Up to kScanOne buckets (meshes up to 320^3) one workgroup does it in one launch; more take three: block-local
+// sort). Up to kScanOne buckets (meshes up to 256^3) one workgroup does it in one launch; more take three: block-local
 // scans of kScanBlock elements (writing block totals), a scan of the block totals, and the add of each block's offset.
+// The line: one workgroup takes 6 us to 200^3, 10.5 at 256^3 (8193 buckets), 13.4 at 270^3 (10405), 16 at 288^3 and 26 at
+// 320^3 (16001), whose 16 loads a thread go out a cache line each; the three launches take 12.5 to 13 at all of these.
 constexpr int kScanPer = 8;
 constexpr int kScanBlock = kNT * kScanPer;
-constexpr int kScanNT = 1024, kScanOnePer = 16;
+constexpr int kScanNT = 1024, kScanOnePer = 10;
 constexpr int kScanOne = kScanNT * kScanOnePer;
 
 __global__ __launch_bounds__(kScanNT) void k_scan_one(int* __restrict__ cnt, int* __restrict__ start, int count,
