@@ -617,6 +617,7 @@ struct ForceProgram {
   struct Pois {
     Section sec;
     int B = 16, M = 8;  // the narrowest width and the most points per thread over the boxes
+    bool fixed = true;  // every box's plan is compiled in
     size_t lds = 0;
   } pois[2];  // [1]: chained
   // The three-spectrum c2r pass, by rows per tile: one launch for the boxes of each width. (At the narrowest width of the
@@ -702,12 +703,13 @@ ForceProgram add_force(JobPack& jp, const std::vector<ForceBox>& boxes, const So
     const ForceBox& b = boxes[ib];
     ForceProgram::Pois& fp = f.pois[chained[ib]];
     fp.M = std::max(fp.M, kern::poisson_points(b.nm, fp.B));
+    fp.fixed = fp.fixed && kern::has_fixed_plan(plan_of(b.nm), fp.B, fp.M);
     ForceProgram::C2R& fc = f.c2r[rows[ib]];
     fc.P = std::max(fc.P, kern::c2r_points(b.nm, rows[ib]));
     fc.lds = std::max(fc.lds, kern::lds_z_c2r(b.nm, 3 * rows[ib]));
     f.Pax = std::max(f.Pax, kern::axis_points(b.nm, f.Bax));
     f.Pz = std::max(f.Pz, kern::r2c_points(b.nm, f.Bz));
-    f.fixed = f.fixed && kern::has_fixed_plan(y_plan_of(b.nm), f.Bax, f.Pax);  // (Pax only grows)
+    f.fixed = f.fixed && kern::has_fixed_plan(y_plan_of(b.nm), f.Bax, f.Pax);  // (Pax and M only grow)
   }
   const int ncopy = cola_run ? 2 : 1;
   std::vector<kern::SortJob> su, sn[2];
@@ -933,7 +935,7 @@ void run_force_mesh(const JobPack& jp, const ForceProgram& f, int c, int* flags,
   for (int ch = 0; ch < 2; ++ch) {
     const ForceProgram::Pois& fp = f.pois[ch];
     if (fp.lds == 0) continue;  // no box takes this form
-    stage("fft x + poisson", s, [&] { return kern::launch_poisson(jp.jobs<kern::PoissonJob>(fp.sec), jp.table(fp.sec), fp.B, fp.M, ch != 0, fp.lds, s); });
+    stage("fft x + poisson", s, [&] { return kern::launch_poisson(jp.jobs<kern::PoissonJob>(fp.sec), jp.table(fp.sec), fp.B, fp.M, ch != 0, fp.fixed, fp.lds, s); });
   }
   stage("fft y inv", s, [&] { return kern::launch_y_grad(jp.jobs<kern::YGradJob>(f.yinv), jp.table(f.yinv), f.Bax, f.Pax, f.fixed, f.lds_ax, s); });
   for (const auto& [r, fc] : f.c2r) {

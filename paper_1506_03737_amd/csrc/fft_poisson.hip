@@ -107,7 +107,9 @@ __device__ __forceinline__ bool x_poisson_chained(float2* tile, float2* tw, cons
 // LDS tile holds them (the registers would spill). The two forms are separate instances because the generic form's
 // register allocation would otherwise cover the chained form's too (and spill). The chained M = 8 instance (the
 // 192-320 meshes) is capped at 80 VGPRs, so that three workgroups fit on a CU (48-box step 30.86 -> 30.25 ms).
-template <int B, int M, bool CHAIN>
+// RT false: every job's plan is compiled in (has_fixed_plan), and the instance has no run-time stages, whose registers cost
+// the compiled ones theirs (384^3, the one such mesh side that does not chain: 204 -> 193 us).
+template <int B, int M, bool CHAIN, bool RT>
 __global__ __launch_bounds__(kFftNT, (CHAIN && M <= 8) ? 6 : ((CHAIN || M <= 12) ? 4 : 2)) void k_fft_x_poisson(
     const PoissonJob* __restrict__ jobs, const int* __restrict__ offs, int njob, int total) {
   constexpr int BP = strided_pitch(B), S = kFftNT / B;
@@ -193,7 +195,7 @@ __global__ __launch_bounds__(kFftNT, (CHAIN && M <= 8) ? 6 : ((CHAIN || M <= 12)
           table_store(tw, r_tw, n, tid);
           table_store(win, r_win, n / 2 + 1, tid);
         };
-        fft_io_fast<false, M, B, BP, true, false>(tile, tw, J.pl, tid, load, none, mid, no_store);
+        fft_io_fast<false, M, B, BP, true, false, false, RT>(tile, tw, J.pl, tid, load, none, mid, no_store);
       }
 
       // Each thread touches only its own points between the barriers that bracket the inverse transforms.
@@ -216,7 +218,7 @@ __global__ __launch_bounds__(kFftNT, (CHAIN && M <= 8) ? 6 : ((CHAIN || M <= 12)
       }
       __syncthreads();
       // first inverse transform: the last stage writes the x gradient to A
-      fft_io_fast<true, M, B, BP, false, true>(tile, tw, J.pl, tid, no_load, none, nothing, store_a);
+      fft_io_fast<true, M, B, BP, false, true, false, RT>(tile, tw, J.pl, tid, no_load, none, nothing, store_a);
       __syncthreads();
       {
         // (the empty asm keeps the comp-invariant indices of the first inverse transform from staying live)
@@ -231,7 +233,7 @@ __global__ __launch_bounds__(kFftNT, (CHAIN && M <= 8) ? 6 : ((CHAIN || M <= 12)
         __syncthreads();
         // the x-transformed potential: the y and z gradients are i k_y and i k_z times it (applied by the y and z
         // passes); the last stage writes it to C
-        fft_io_fast<true, M, B, BP, false, true>(tile, tw, J.pl, ltid, no_load, none, nothing, store_c);
+        fft_io_fast<true, M, B, BP, false, true, false, RT>(tile, tw, J.pl, ltid, no_load, none, nothing, store_c);
       }
     }
   }
@@ -239,16 +241,23 @@ __global__ __launch_bounds__(kFftNT, (CHAIN && M <= 8) ? 6 : ((CHAIN || M <= 12)
 
 struct Init {
   Init() {
-    allow_big_lds(k_fft_x_poisson<8, 8, true>);
-    allow_big_lds(k_fft_x_poisson<8, 12, true>);
-    allow_big_lds(k_fft_x_poisson<8, 16, true>);
-    allow_big_lds(k_fft_x_poisson<4, 8, false>);
-    allow_big_lds(k_fft_x_poisson<8, 8, false>);
-    allow_big_lds(k_fft_x_poisson<8, 12, false>);
-    allow_big_lds(k_fft_x_poisson<8, 16, false>);
-    allow_big_lds(k_fft_x_poisson<16, 8, false>);
-    allow_big_lds(k_fft_x_poisson<16, 12, false>);
-    allow_big_lds(k_fft_x_poisson<16, 16, false>);
+    allow_big_lds(k_fft_x_poisson<8, 8, true, false>);
+    allow_big_lds(k_fft_x_poisson<8, 12, true, false>);
+    allow_big_lds(k_fft_x_poisson<8, 16, true, false>);
+    allow_big_lds(k_fft_x_poisson<4, 8, false, false>);
+    allow_big_lds(k_fft_x_poisson<4, 8, false, true>);
+    allow_big_lds(k_fft_x_poisson<8, 8, false, false>);
+    allow_big_lds(k_fft_x_poisson<8, 8, false, true>);
+    allow_big_lds(k_fft_x_poisson<8, 12, false, false>);
+    allow_big_lds(k_fft_x_poisson<8, 12, false, true>);
+    allow_big_lds(k_fft_x_poisson<8, 16, false, false>);
+    allow_big_lds(k_fft_x_poisson<8, 16, false, true>);
+    allow_big_lds(k_fft_x_poisson<16, 8, false, false>);
+    allow_big_lds(k_fft_x_poisson<16, 8, false, true>);
+    allow_big_lds(k_fft_x_poisson<16, 12, false, false>);
+    allow_big_lds(k_fft_x_poisson<16, 12, false, true>);
+    allow_big_lds(k_fft_x_poisson<16, 16, false, false>);
+    allow_big_lds(k_fft_x_poisson<16, 16, false, true>);
   }
 };
 
@@ -256,25 +265,34 @@ struct Init {
 
 void init_poisson() { static Init once; }
 
-hipError_t launch_poisson(const PoissonJob* jobs, WorkTable wt, int B, int M, bool chained, size_t lds, hipStream_t s) {
+hipError_t launch_poisson(const PoissonJob* jobs, WorkTable wt, int B, int M, bool chained, bool fixed_plans, size_t lds,
+                          hipStream_t s) {
   init_poisson();
   if (wt.total <= 0) return hipSuccess;
   const unsigned g = static_cast<unsigned>(wt.total);
-#define LPC_POIS(BB, MM, CC) k_fft_x_poisson<BB, MM, CC><<<g, kFftNT, lds, s>>>(jobs, wt.offs, wt.njob, wt.total)
+#define LPC_POIS(BB, MM, CC, RR) k_fft_x_poisson<BB, MM, CC, RR><<<g, kFftNT, lds, s>>>(jobs, wt.offs, wt.njob, wt.total)
+#define LPC_POIS_P(BB, MM)                  \
+  {                                         \
+    if (fixed_plans)                        \
+      LPC_POIS(BB, MM, false, false);       \
+    else                                    \
+      LPC_POIS(BB, MM, false, true);        \
+  }
   if (chained) {
-    if (B == 8 && M == 8) LPC_POIS(8, 8, true);
-    else if (B == 8 && M == 12) LPC_POIS(8, 12, true);
-    else if (B == 8 && M == 16) LPC_POIS(8, 16, true);
+    if (B == 8 && M == 8) LPC_POIS(8, 8, true, false);
+    else if (B == 8 && M == 12) LPC_POIS(8, 12, true, false);
+    else if (B == 8 && M == 16) LPC_POIS(8, 16, true, false);
     else return hipErrorInvalidValue;
   }
-  else if (B == 4 && M == 8) LPC_POIS(4, 8, false);
-  else if (B == 8 && M == 8) LPC_POIS(8, 8, false);
-  else if (B == 8 && M == 12) LPC_POIS(8, 12, false);
-  else if (B == 8 && M == 16) LPC_POIS(8, 16, false);
-  else if (B == 16 && M == 8) LPC_POIS(16, 8, false);
-  else if (B == 16 && M == 12) LPC_POIS(16, 12, false);
-  else if (B == 16 && M == 16) LPC_POIS(16, 16, false);
+  else if (B == 4 && M == 8) LPC_POIS_P(4, 8)
+  else if (B == 8 && M == 8) LPC_POIS_P(8, 8)
+  else if (B == 8 && M == 12) LPC_POIS_P(8, 12)
+  else if (B == 8 && M == 16) LPC_POIS_P(8, 16)
+  else if (B == 16 && M == 8) LPC_POIS_P(16, 8)
+  else if (B == 16 && M == 12) LPC_POIS_P(16, 12)
+  else if (B == 16 && M == 16) LPC_POIS_P(16, 16)
   else return hipErrorInvalidValue;
+#undef LPC_POIS_P
 #undef LPC_POIS
   return hipGetLastError();
 }

@@ -338,7 +338,8 @@ hipError_t launch_axis(const AxisJob* jobs, WorkTable wt, bool inverse, int B, i
                        hipStream_t s);
 hipError_t launch_y_grad(const YGradJob* jobs, WorkTable wt, int B, int P, bool fixed_plans, size_t lds, hipStream_t s);
 // chained: every job's plan is poisson_chainable and B = 8 (the transforms chained through registers)
-hipError_t launch_poisson(const PoissonJob* jobs, WorkTable wt, int B, int M, bool chained, size_t lds, hipStream_t s);
+hipError_t launch_poisson(const PoissonJob* jobs, WorkTable wt, int B, int M, bool chained, bool fixed_plans, size_t lds,
+                          hipStream_t s);
 // Whether the fused x pass can chain the plan's transforms through registers (LPC_CHAINED_PLANS, on 8-column tiles; at
 // the points per thread that poisson_points gives, every such plan fits).
 bool poisson_chainable(const Plan1D& pl);
