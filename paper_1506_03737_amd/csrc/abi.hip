@@ -282,13 +282,14 @@ lpc_fft_tiling default_tiling(int n) {
   // 16 columns rather than 32 above n = 200 (inverse y at 240^3 77 -> 68 us, at 256^3 68 -> 62; equal at 200^3)
   t.axis_cols = n <= 200 ? 32 : kern::strided_cols(n, 16);
   // The fused x pass keeps psi_hat in registers up to 12 points per thread; above that it holds a second tile in LDS and
-  // has one workgroup per CU: 16 columns to n = 384, 8 to 768, 4 above (400^3 587 us with 16 and 376 with 8, 512^3 907
-  // and 593; 864^3 6.5 ms with 8 and 4.3 with 4, 960^3 8.0 and 5.5; at 360^3 256 with 16 and 284 with 8). The chained
+  // has one workgroup per CU: 16 columns below n = 384, 8 to 768, 4 above (360^3 256 us with 16 and 284 with 8, 384^3 193 and
+  // 186, 400^3 567 and 367, 512^3 907 and 593; 864^3 6.5 ms with 8 and 4.3 with 4, 960^3 8.0 and 5.5). The chained
   // form takes 8 columns at any size (256^3 60 -> 50, 320^3 112 -> 90; a batch of 192, 256 and 320 3.36 -> 3.18 ms).
-  t.poisson_cols = kern::poisson_chainable(plan_of(n)) ? 8 : (n <= 384 ? 16 : (n <= 768 ? 8 : 4));
-  // Fewer rows than fit put more workgroups on a CU: 16 to n = 240, 8 to 480, 4 above (240^3 86 us with either, 256^3 99
-  // with 16 and 88 with 8, 300^3 176 and 151; 480^3 566 with 8 and 640 with 4, 512^3 736 and 684, 600^3 1227 and 1101).
-  t.c2r_rows = n <= 240 ? 16 : (n <= 480 ? 8 : 4);
+  t.poisson_cols = kern::poisson_chainable(plan_of(n)) ? 8 : (n < 384 ? 16 : (n <= 768 ? 8 : 4));
+  // Fewer rows than fit put more workgroups on a CU: 16 to n = 240, 8 to 486, 4 above (240^3 81 us with 16 and 82 with 8,
+  // 250^3 105 and 93, 300^3 173 and 150; 480^3 565 with 8 and 620 with 4, 486^3 606 and 695, 500^3 743 and 702, 512^3 728 and
+  // 678, 600^3 1196 and 1081).
+  t.c2r_rows = n <= 240 ? 16 : (n <= 486 ? 8 : 4);
   return t;
 }
 
