@@ -1500,6 +1500,8 @@ lpc_status lpc_cola_step_batched(const lpc_batch_entry* entries, int32_t n_real,
       b.C = reinterpret_cast<float2*>(base + round_up(M * 12) + 2 * cbytes);
       boxes.push_back(b);
     }
+    // before the widths are read: a change between the two then gives the next call another key, not this graph
+    const uint64_t tgen = tiling_generation();
     const ForceProgram f = add_force(jp, boxes, ss, step->deconv_power, true);
     jp.upload(s);
     stage("clear", s, [&] { return kern::clear_call(flags, f.ss.cnt, f.ss.G, s); });
@@ -1519,7 +1521,6 @@ lpc_status lpc_cola_step_batched(const lpc_batch_entry* entries, int32_t n_real,
     put(step, sizeof(*step));
     put(a_list, sizeof(double) * n_a);
     put(&ws, sizeof(ws));
-    const uint64_t tgen = tiling_generation();
     put(&tgen, sizeof(tgen));
     if (g_graph.exec == nullptr || g_graph.key != key) {
       if (g_graph.exec) {
