@@ -63,7 +63,7 @@ TIE = 0.03  # widths timed within 3 % of the fastest count as tied
 def pick(times, tie=TIE):
     """The width to use from {width: ms}: the widest one within `tie` of the fastest. Widths that close are within
     the timing noise of one tuning round, and the wider tile is kept because a batched launch runs every box at the
-    narrowest width any of its mesh sizes was given."""
+    narrowest width any of its mesh sizes was given (the c2r pass, whose boxes keep their own width, excepted)."""
     fastest = min(times.values())
     return max(w for w, t in times.items() if t <= fastest * (1.0 + tie))
 

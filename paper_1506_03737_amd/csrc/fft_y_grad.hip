@@ -15,7 +15,8 @@ namespace {
 // Items of component 1 take B / 2 columns of the x-transformed potential psi from C and stack them twice in their
 // tile, as i k_y psi (columns b) and as psi (columns B / 2 + b): one B-column transform gives the y gradient, stored
 // to B, and psi, stored back to C (k_z is constant along y; the z pass applies i k_z as it loads C). An item reads and
-// writes only its own columns, so items do not race.
+// writes only its own columns, so items do not race. At 80 registers the 8-point instances with run-time stages spill 2, which
+// costs less than a wave per SIMD: without the cap 100^3 takes 15.7 us instead of 12.9, 200^3 (16 columns) 47 instead of 44.
 template <int B, int EPT, bool RT>
 __global__ __launch_bounds__(kFftNT, EPT <= 8 ? 6 : 4) void k_fft_y_grad(
     const YGradJob* __restrict__ jobs, const int* __restrict__ offs, int njob, int total) {

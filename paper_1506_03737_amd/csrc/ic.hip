@@ -8,7 +8,9 @@
 // xy, 1, y, yy), and only the z pass, which holds all six of a row, forms the nine real rows (Psi1 and the six phi_ij),
 // the source and its forward z transform. The spectrum is zero on every Nyquist plane, so the passes leave the kz = N/2
 // column out. Per lattice site (256^3, bytes): 14 transforms with their factor passes moved about 540, these passes
-// about 210; the construction is bound by those bytes (and the white noise by its FP64 arithmetic).
+// about 210, which is 0.71 ms at the card's copy rate. The passes take 1.14 ms: the x and y passes run near that rate, the
+// first z pass (343 us for 140 us of bytes) is bound by the VALU and LDS work of its nine run-time transforms a row, and the
+// white noise by its FP64 arithmetic.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -376,6 +378,9 @@ struct IcZShape<kIcPlain> {
 
 __device__ __forceinline__ float2 times_i(float2 v, float s) { return make_float2(-s * v.y, s * v.x); }  // i s v
 
+// The cap of 80 registers spills 17 (kIcFirst) and 7 (kIcSecond) of them, and is still the better one: without spills, at 5
+// waves per SIMD, the first group takes 45 us instead of 41 at 128^3, 86 and 80 at 160^3, 131 and 140 at 192^3, 345 and 343
+// at 256^3, 521 and 434 at 270^3, 2700 and 2591 at 512^3; the second 281 and 301 at 270^3, 1760 and 1777 at 512^3.
 template <int MODE>
 __global__ __launch_bounds__(kFftNT, 6) void k_ic_z(IcZ a) {
   using Sh = IcZShape<MODE>;

@@ -390,7 +390,7 @@ constexpr int kMaxC = 64;  // channels of the widest layer
 // and, for the bias, the four lane groups are summed in a fixed order at the end. Bricks that reach past the grid hold
 // zeros there, so any D takes this kernel. (Sides that are no multiple of 32 used to run on the vector ALUs, one voxel
 // product per lane, and took most of a training step: one loss and gradient at 32^3 966 -> 538 us, at 64^3 1171 -> 755, at
-// 72^3 2943 -> 927; at 8^3, nearly all padding, 472 -> 484.)
+// 72^3 2943 -> 927; at 8^3, nearly all padding, 492 and 493.)
 constexpr int kWB = 32;                    // z extent of a brick: one K step
 constexpr int kWRow = 20;                  // halo row pitch in dwords (17 used; a multiple of 4 for 16-byte reads)
 constexpr int kWXC = 36 * kWRow + 20;      // halo channel pitch in dwords, = 4 mod 32: 8 lanes' 16-byte reads hit
