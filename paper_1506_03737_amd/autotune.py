@@ -71,8 +71,10 @@ def pick(times, tie=TIE):
 def tune(n_mesh, device="cuda", reps=5, box=1000.0, seed=0, log=None):
     """Measure every fitting width of every pass at mesh size n_mesh and set the fastest (see pick) as the override.
 
-    The passes are separate kernels, so round i runs every field at its i-th candidate (the last one repeated when a
-    field has fewer) and each field is ranked by its own stages' times: max(len(candidates)) rounds in all.
+    One field at a time, in the order of FIELDS, with the others at what they will run at (the built-in width, or the one
+    already picked): a pass finds the caches as the pass before it left them, and ranked behind another pass's slowest
+    width the c2r of 320^3 looked 6 % faster at 4 rows than at 8, which a run at the picked widths loses again (48 boxes
+    of 192, 256 and 320: 82.4 ms per three evaluations with 8 rows, 85.8 with 4).
     Returns {"n_mesh", "tiling", "default", "stage_ms": {field: {width: ms}}, "seconds"}."""
     import torch
     t0 = time.perf_counter()
@@ -91,19 +93,19 @@ def tune(n_mesh, device="cuda", reps=5, box=1000.0, seed=0, log=None):
 
     timings = {f: {} for f in FIELDS}
     saved = lpc.lpc_fft_tiling_get(n_mesh)
+    best = dict(base)
     try:
-        for i in range(max(len(c) for c in cands.values())):
-            t = {f: cands[f][min(i, len(cands[f]) - 1)] for f in FIELDS}
-            lpc.lpc_fft_tiling_set(n_mesh, t)
-            run()  # warm-up under this tiling
-            torch.cuda.synchronize()
-            ms = _stage_ms(run, reps)
-            for f, (stages, _) in FIELDS.items():
-                timings[f].setdefault(t[f], sum(ms[s] for s in stages))
+        for f, (stages, _) in FIELDS.items():
+            for w in cands[f]:
+                lpc.lpc_fft_tiling_set(n_mesh, dict(best, **{f: w}))
+                run()  # warm-up under this tiling
+                torch.cuda.synchronize()
+                ms = _stage_ms(run, reps)
+                timings[f][w] = sum(ms[s] for s in stages)
+            best[f] = pick(timings[f])
     except BaseException:
         lpc.lpc_fft_tiling_set(n_mesh, None if saved == base else saved)
         raise
-    best = {f: pick(timings[f]) for f in FIELDS}
     lpc.lpc_fft_tiling_set(n_mesh, best)
     res = {"n_mesh": n_mesh, "tiling": best, "default": base,
            "stage_ms": {f: {str(w): round(v, 4) for w, v in timings[f].items()} for f in FIELDS},
