@@ -219,8 +219,10 @@ def batched_bench(lpc, synth, torch):
         per = [stage_bytes(name, b["n_side"] ** 3, b["n_mesh"]) for b in boxes]
         avg = ms / launches
         entry = {"launches": launches, "avg_ms": round(avg, 4), "share": round(ms / (dt_prof * 1e3), 4)}
-        if per[0] is not None:
-            entry["GB_per_s"] = round(sum(per) / (avg * 1e-3) / 1e9, 1)
+        if name in PER_EVALUATION:
+            entry["ms_per_evaluation"] = round(ms / (steps + 1), 4)
+        if per[0] is not None:  # (a stage may take several launches an evaluation: one per form or width of its boxes)
+            entry["GB_per_s"] = round(sum(per) * launch_share(name, launches, steps + 1) / (avg * 1e-3) / 1e9, 1)
         stages[name] = entry
     return {"value": n_total * steps / dt, "unit": "particle-steps/s", "ms_per_step": dt * 1e3 / steps,
             "steps": steps, "boxes": len(boxes), "particles": n_total,
