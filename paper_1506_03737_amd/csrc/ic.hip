@@ -9,8 +9,8 @@
 // the source and its forward z transform. The spectrum is zero on every Nyquist plane, so the passes leave the kz = N/2
 // column out. Per lattice site (256^3, bytes): 14 transforms with their factor passes moved about 540, these passes
 // about 210, which is 0.71 ms at the card's copy rate. The passes take 1.14 ms: the y passes run at 0.85 of that rate, the x
-// passes at 0.55, the first z pass (343 us for 140 us of bytes) is bound by the VALU and LDS work of its nine run-time
-// transforms a row, and the white noise by its FP64 arithmetic.
+// passes at 0.55, the first z pass (343 us for 135 us of bytes) is bound by the VALU and LDS work of its nine run-time
+// transforms a row and by the 0.6 GB that its spilled registers add, and the white noise by its FP64 arithmetic.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
