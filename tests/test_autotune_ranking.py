@@ -2,17 +2,17 @@
 pass before it leaves in the caches. Stage times here are a made-up function of the tiling in effect; no GPU."""
 import pytest
 
-from paper_1506_03737_amd import autotune, lpc
-
 
 @pytest.fixture(autouse=True)
 def builtin_tiling_after():
     yield
+    from paper_1506_03737_amd import lpc
     lpc.lpc_fft_tiling_reset()
 
 
 def test_pass_behind_another_is_ranked_at_the_picked_width(monkeypatch):
     import torch
+    from paper_1506_03737_amd import autotune, lpc
     nm = 192
     seen = []
 

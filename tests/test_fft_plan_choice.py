@@ -5,8 +5,6 @@ import ctypes
 
 import pytest
 
-from paper_1506_03737_amd import lpc
-
 STAGES = 7
 
 
@@ -16,6 +14,7 @@ class Plan1D(ctypes.Structure):
 
 
 def functions():
+    from paper_1506_03737_amd import lpc
     make = getattr(lpc.LIB, "_ZN3lpc4kern9make_planEiPNS0_6Plan1DEb")
     make.restype, make.argtypes = ctypes.c_bool, [ctypes.c_int, ctypes.POINTER(Plan1D), ctypes.c_bool]
     fixed = getattr(lpc.LIB, "_ZN3lpc4kern14has_fixed_planERKNS0_6Plan1DEii")

@@ -1,14 +1,14 @@
 """The built-in tile widths on either side of each measured line (host only; what each side took stands at the rule)."""
 import pytest
 
-from paper_1506_03737_amd import lpc
-
 
 @pytest.mark.parametrize("nm,rows", [(240, 16), (250, 8), (480, 8), (486, 8), (500, 4), (1024, 4)])
 def test_c2r_rows(nm, rows):
+    from paper_1506_03737_amd import lpc
     assert lpc.lpc_fft_tiling_default(nm)["c2r_rows"] == rows
 
 
 @pytest.mark.parametrize("nm,cols", [(192, 8), (200, 16), (256, 8), (360, 16), (384, 8), (720, 8), (768, 8), (800, 4), (1024, 8)])
 def test_poisson_cols(nm, cols):
+    from paper_1506_03737_amd import lpc
     assert lpc.lpc_fft_tiling_default(nm)["poisson_cols"] == cols
