@@ -674,15 +674,17 @@ kern::DepSplit dep_split(char* base, size_t bytes, const kern::TileGrid& nt, int
   sp.entries = static_cast<int>(std::min<size_t>(entries, 1 << 28));
   // Chunks of 4096 particles (16 per thread). The chunks' kernel runs before the whole tiles', and a chunk adds 4096 cells
   // through memory, so a tile is split only when as one workgroup it would outlast everything else: past 8192 particles,
-  // past four times a tile's mean share, and past n / 400. (What counts is the particles that reach a tile, its own and the
-  // boundary buckets of seven neighbours, 2.4 shares in a uniform set; with about 1000 workgroups on the chip the whole takes
-  // as long as one of 2.4 n / 1000.) Where many tiles are heavy the whole is longer than any of them, and splitting costs:
-  // without the last term, 256^3 late and clustered on 512^3 took 622 us for 356 unsplit (357 with it), on 256^3 887 for 273
-  // (275). With n / 200, 400, 800 and none: 16 M half in 200 clumps on 256^3 700, 530, 661 and 726 us (unsplit 2729), 50 M in
-  // eight clumps on 480^3 2564, 2920, 3190 and 4100 (3692), later 256^3 on 512^3 671, 556, 773 and 1326 (804). Four shares
-  // against 6 and 10: 4 M half in 200 clumps on 128^3 146, 160 and 382 us (764).
+  // past four times a tile's mean share, and past n / 400 (or 2^16, where a whole tile walks its particles twice). (What
+  // counts is the particles that reach a tile, its own and the boundary buckets of seven neighbours, 2.4 shares in a uniform
+  // set; with about 1000 workgroups on the chip the whole takes as long as one of 2.4 n / 1000.) Where many tiles are heavy
+  // the whole is longer than any of them, and splitting costs: without the third term, 256^3 late and clustered on 512^3 took
+  // 622 us for 356 unsplit (357 with it), on 256^3 887 for 273 (275). With n / 200, 400, 800 and none: 16 M half in 200 clumps
+  // on 256^3 700, 530, 661 and 726 us (unsplit 2729), later 256^3 on 512^3 671, 556, 773 and 1326 (804). 50 M on 480^3, with
+  // the bound of 2^16, without it and with no third term: half in 500 clumps 1529, 1694 and 2778 (3717), 70 % in eight narrow
+  // clumps 3873, 4259 and 3784 (11796). Four shares against 6 and 10: 4 M half in 200 clumps on 128^3 146, 160 and 382 us (764).
   sp.size = 4096;
-  sp.trigger = static_cast<int>(std::min<int64_t>(INT32_MAX, std::max<int64_t>({8192, 4 * n / nt.count(), n / 400})));
+  const int64_t whole = std::min<int64_t>(n / 400, (1 << 16) - 1);
+  sp.trigger = static_cast<int>(std::min<int64_t>(INT32_MAX, std::max<int64_t>({8192, 4 * n / nt.count(), whole})));
   return sp;
 }
 

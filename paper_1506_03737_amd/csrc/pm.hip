@@ -485,7 +485,7 @@ __global__ __launch_bounds__(kNT) void k_scatter(const SortJob* __restrict__ job
 // ranges are walked as one index space, so a workgroup needs few rounds of loads.
 // A tile that holds many more particles than the others would keep one workgroup busy long after the rest: it is split
 // (mark_split_tiles), the chunks' workgroups add their counts in a slot with global atomics, and the last to arrive writes
-// the tile (70 % of the particles in eight clumps: 1.5 M on 270^3 0.63 -> 0.12 ms, 50 M on 480^3 11.8 -> 3.7 ms; each
+// the tile (70 % of the particles in eight clumps: 1.5 M on 270^3 0.63 -> 0.14 ms, 50 M on 480^3 11.8 -> 3.9 ms; each
 // chunk in a slot of its own, summed by the last, grew with the square of a tile's chunks: 22 ms).
 // 1024 threads per tile (for meshes of few, full tiles) measured slower: 16.7 M particles on 128^3 0.47 -> 0.60 ms.
 // A cell's exact count C is a sum of corner weights of at most 2^48 each. With fewer than 2^16 particles reaching a

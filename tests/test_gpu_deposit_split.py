@@ -25,7 +25,7 @@ def split_plan(nm, n):
     room = 12 * nm**3 - up(4 * nm**3)
     entries = room // 64
     slots = (room - up(8) - up(4 * tiles) - up(8 * entries) - 512) // (2 * 4096 * 8 + 4)
-    return slots, entries, max(8192, 4 * n // tiles, n // 400)
+    return slots, entries, max(8192, 4 * n // tiles, min(n // 400, 65535))
 
 
 def reach(pos, nm, box):
